@@ -35,6 +35,7 @@
 
 #include <cstdlib>
 #include "common.hpp"
+#include "gemm_tile.hpp"
 #include "kernels.hpp"
 
 namespace gp {
@@ -46,14 +47,6 @@ template <> struct Frag<bf16> {
     bf16x8 v;
     __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const bf16x8*>(p); }
 };
-template <> struct Frag<float> {
-    f32x4 lo, hi;
-    __device__ __forceinline__ void load(const float* p) {
-        lo = *reinterpret_cast<const f32x4*>(p);
-        hi = *reinterpret_cast<const f32x4*>(p + 4);
-    }
-};
-
 // One 32x32 output block advanced by 16 reduction steps.  Lane l supplies row
 // (l % 32) of A and column (l % 32) of B over the 8 k-values
 // [8 (l / 32), 8 (l / 32) + 8) of the 16-step chunk; A and B use the same
@@ -67,34 +60,13 @@ __device__ __forceinline__ void mma16(f32x16& c, const Frag<bf16>& a, const Frag
     c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a.v), __builtin_bit_cast(f16x8, b.v), c, 0,
                                                0, 0);
 }
-__device__ __forceinline__ void mma(f32x16& c, const Frag<float>& a, const Frag<float>& b) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.lo[e], b.lo[e], c, 0, 0, 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.hi[e], b.hi[e], c, 0, 0, 0);
-}
-
 template <typename T> using V16 = typename Vec16<T>::type;
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef __amdgpu_buffer_rsrc_t Rsrc;
 
-// Buffer resource over `bytes` bytes at p; raw buffer accesses beyond it read
-// 0 and drop writes, which implements the tile-edge masking without branches.
-constexpr uint32_t OOB = 0x80000000u;
-__device__ __forceinline__ Rsrc make_rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
 template <typename T>
 __device__ __forceinline__ V16<T> bload16(Rsrc r, uint32_t off) {
     return __builtin_bit_cast(V16<T>, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
-// LDS tiles hold ROWS rows of BK elements (128 bytes) with no padding; the
-// 16-byte chunk c of row r is stored at chunk c ^ swz(r).  swz varies over
-// any 8 consecutive rows (conflict-free fragment reads, where 8 lanes read 8
-// consecutive rows) and over rows 8 apart (conflict-free transposing stores,
-// where 8 lanes write rows 8 apart).
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 // fp4 rows of a stage are 32 bytes (two 16-byte chunks); swapping the chunks
 // of rows 8 .. 15 (mod 16) spreads 16 lanes reading 16 consecutive rows over
 // all banks
@@ -210,7 +182,6 @@ struct TileLoader {
 
 template <typename T> struct GemmCfg;
 template <> struct GemmCfg<bf16> { static constexpr int BK = 64; };
-template <> struct GemmCfg<float> { static constexpr int BK = 32; };
 
 // Fragment read: 8 elements (16 bytes for bf16, 32 for fp32) of one LDS row.
 template <typename T> struct FragRead;
@@ -219,13 +190,6 @@ template <> struct FragRead<bf16> {
         f.v = *reinterpret_cast<const bf16x8*>(s + lds_byte(row, kbyte));
     }
 };
-template <> struct FragRead<float> {
-    static __device__ __forceinline__ void load(Frag<float>& f, const char* s, int row, int kbyte) {
-        f.lo = *reinterpret_cast<const f32x4*>(s + lds_byte(row, kbyte));
-        f.hi = *reinterpret_cast<const f32x4*>(s + lds_byte(row, kbyte + 16));
-    }
-};
-
 // Fused epilogue of one workgroup tile through buffer resources (out-of-range
 // elements are dropped by the hardware).  Inputs are loaded in batches of one
 // 32-row block strip (TN x 16 values per lane) before any store of that strip,
@@ -507,40 +471,6 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs args) {
 // issued.  NSTAGE stages form a ring; k-tile t + NSTAGE - 1 is in flight while
 // tile t is consumed.  Waits use explicit vmcnt values (loads complete in
 // order), and the single barrier per k-tile precedes the last k-step's MFMAs.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt");
-    __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
-    switch (n) {
-    case 0: wait_vmcnt<0>(); break;
-    case 4: wait_vmcnt<4>(); break;
-    case 5: wait_vmcnt<5>(); break;
-    case 6: wait_vmcnt<6>(); break;
-    case 10: wait_vmcnt<10>(); break;
-    case 20: wait_vmcnt<20>(); break;
-    case 8: wait_vmcnt<8>(); break;
-    case 12: wait_vmcnt<12>(); break;
-    case 16: wait_vmcnt<16>(); break;
-    case 24: wait_vmcnt<24>(); break;
-    case 32: wait_vmcnt<32>(); break;
-    case 48: wait_vmcnt<48>(); break;
-    default: wait_vmcnt<0>(); break;
-    }
-}
-
-// All waves of the workgroup meet once every LDS read of this wave has
-// returned.  No memory fence: a fence would also wait for every outstanding
-// direct-to-LDS load of the wave (vmcnt(0)) and so drain the prefetch ring;
-// the loads a k-tile needs are waited for explicitly (wait_vmcnt) before.
-// The memory clobber keeps the compiler from moving LDS accesses across it.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-typedef __attribute__((address_space(3))) void* LdsPtr;
-
 // P direct loads of 8 rows (1 KB) each into consecutive LDS blocks at dst;
 // lane offsets vo[i] are fixed, the k advance is the scalar offset so.
 template <int P>
@@ -578,10 +508,6 @@ __device__ __forceinline__ void dl_issue_part(int part, Rsrc A, Rsrc B, const ui
         }
     }
 }
-
-// Wave index as a wave-uniform (scalar) value, so LDS base addresses derived
-// from it stay in SGPRs (M0 of the direct loads).
-__device__ __forceinline__ int uniform_wave_id(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
 
 // Epilogue of a tile lying entirely inside C: per-lane column offsets are
 // computed once; the row part of every offset is wave-uniform and passed as
@@ -720,25 +646,16 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
     const int kg = wave_all / NW, wave = wave_all % NW;  // k-group, wave within the group
     char* const smem = smem_all + kg * NSTAGE * STAGE;   // the group's stage ring
     const int wm = wave / WN, wn = wave % WN;
-    const int tiles_m = (args.M + BM - 1) / BM;
+    const int tiles_m = (args.M + BM - 1) / BM, tiles_n = (args.N + BN - 1) / BN;
+    // The band height H of the tile order suits the tiles an XCD runs at once
+    // (P: its 32 CUs times the workgroups that fit a CU): about sqrt(P BN / BM)
+    // rows (a run down whole tile columns would stream all of A through every
+    // XCD; 4 x 8 tiles for 32 workgroups).
     const int G = gridDim.x;
-    int bid = blockIdx.x;
-    const int G8 = G & ~7;
-    if (bid < G8) bid = (bid & 7) * (G8 >> 3) + (bid >> 3);
-    // XCD x now holds a contiguous run of ids; number the tiles in bands of
-    // H tile rows, column by column within a band, so that the tiles one XCD
-    // runs at a time form a compact block (4 x 8 for 32 workgroups) and its
-    // L2 serves each A row panel and B column panel to several of them
-    // (a run down whole tile columns would stream all of A through every XCD)
-    // The band height H suits the tiles an XCD runs at once (P: its 32 CUs
-    // times the workgroups that fit a CU): about sqrt(P BN / BM) rows.
     constexpr int RES = (160 * 1024) / (KG * NSTAGE * STAGE) < 1 ? 1 : (160 * 1024) / (KG * NSTAGE * STAGE);
     const int P = min(max(G >> 3, 1), 32 * min(RES, 3));
-    const int H = P * BN >= 64 * BM ? 8 : 4;
-    const int tiles_n = (args.N + BN - 1) / BN;
-    const int band = bid / (H * tiles_n), in_band = bid - band * H * tiles_n;
-    const int bh = min(H, tiles_m - band * H);
-    const int tm = band * H + in_band % bh, tn = in_band / bh;
+    int tm, tn;
+    band_tile(blockIdx.x, G, tiles_m, tiles_n, P * BN >= 64 * BM ? 8 : 4, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
     const int nk_all = args.K / BK;
@@ -1666,8 +1583,7 @@ gp_status gemm(const GemmArgs& a, int epi, bool a_kmajor, bool b_kmajor, int dty
     }
     gp_status s = check_args<float>(a, a_kmajor, b_kmajor);
     if (s != GP_OK) return s;
-    return a_kmajor ? launch_tile<float, 128, 128, true, true>(a, epi, 1, st)
-                    : launch_tile<float, 128, 128, false, false>(a, epi, 1, st);
+    return gemm_f32(a, epi, a_kmajor, st);
 }
 
 } // namespace gp

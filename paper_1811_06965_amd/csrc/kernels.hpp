@@ -58,6 +58,9 @@ struct GemmArgs {
 };
 
 gp_status gemm(const GemmArgs& a, int epi, bool a_kmajor, bool b_kmajor, int dtype, hipStream_t st);
+// The fp32 GEMM (gemm_f32.hip), operands of one majorness (k_major: both
+// k-contiguous); no split-K: ws is not used.  Arguments checked by gemm().
+gp_status gemm_f32(const GemmArgs& a, int epi, bool k_major, hipStream_t st);
 // Floats of a.ws that gemm() with these arguments writes (its split-K partial
 // tiles and column-sum rows); 0 when it runs unsplit.  Host arithmetic only.
 long gemm_workspace_need(const GemmArgs& a, int epi, bool a_kmajor, int dtype);

@@ -1,0 +1,61 @@
+"""fp32 kernels at the edges of their tiles, against the fp64 oracle and each other."""
+import numpy as np
+import pytest
+
+import synth
+from parity import compare_grads, rel_err, to_np
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _step(cfg, case):
+    from paper_1811_06965_amd.runtime import Partition
+    with Partition(cfg) as part:
+        part.load_params(case["layers"], case["head"])
+        inp = part.device_inputs(case)
+        out = part.step(inp["x"], inp["mem"], inp["dy"])
+        torch.cuda.synchronize()
+        gl, gh = part.grads()
+    return dict(y=to_np(out["y"]), dx=to_np(out["dx"]), loss=out["loss"], grads=gl, head=gh)
+
+
+def _against_oracle(cfg, case, res):
+    """The fp32 parity bound of 1e-4 that every fp32 partition is held to."""
+    from oracle import gpipe
+    ref = gpipe.gpipe_step(cfg, case, cfg.micro)
+    assert rel_err(res["y"], ref["y"]) <= 1e-4
+    assert rel_err(res["dx"], ref["dx"]) <= 1e-4
+    assert abs(res["loss"] - ref["loss"]) <= 1e-4 * abs(ref["loss"])
+    compare_grads(res["grads"], res["head"], ref["grads"], ref["head_grads"], "rel", 1e-4)
+
+
+# widths and rows that are no multiples of a tile or of a 32-deep k-tile, and
+# rows of several 128-row tiles; the reductions end 4, 8, 12, 16 .. past a k-tile
+GEMM_CASES = {
+    "edges": synth.PartitionConfig("edges", layers=1, d_model=72, d_ff=200, heads=6, seq=20, batch=6, micro=3,
+                                   dtype="f32", kind="decoder", loss="xent_ls", vocab=104, label_smoothing=0.1,
+                                   mem_seq=12),
+    "wide": synth.PartitionConfig("wide", layers=2, d_model=144, d_ff=328, heads=4, seq=68, batch=10, micro=2,
+                                  dtype="f32", loss="mse"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(GEMM_CASES))
+def test_f32_gemm_tiles_agree_bit_for_bit(name, monkeypatch):
+    """Every tile sums each element in the same order, so forcing any of them
+    gives the same bits; one of them against the oracle."""
+    cfg = GEMM_CASES[name]
+    case = synth.make_case(cfg, 1, perturb=True)
+    res = []
+    for tile in (32, 33, 34):
+        monkeypatch.setenv("GP_GEMM_TILE", str(tile))
+        res.append(_step(cfg, case))
+    _against_oracle(cfg, case, res[0])
+    for r in res[1:]:
+        assert np.array_equal(r["y"], res[0]["y"]) and np.array_equal(r["dx"], res[0]["dx"])
+        assert r["loss"] == res[0]["loss"]
+        for a, b in zip(r["grads"] + [r["head"]], res[0]["grads"] + [res[0]["head"]]):
+            for k in a:
+                assert np.array_equal(a[k], b[k]), k
