@@ -137,8 +137,8 @@ gp_status cast_out(int dtype, const float* src, void* dst, long count, hipStream
 gp_status mse_grad(int dtype, const float* y, const void* target, long count, double norm, float* d32,
                    void* delt, double* partial, int* nblk, hipStream_t st);
 int loss_blocks();
-// acc[0] = (accumulate ? acc[0] : 0) + sum_b partial[b]
-gp_status loss_finalize(const double* partial, int nblk, double* acc, int accumulate, hipStream_t st);
+// acc[0] = sum over m < M, b < used of partial[m stride + b]
+gp_status loss_finalize(const double* partial, long stride, int used, int M, double* acc, hipStream_t st);
 
 // Label-smoothed softmax cross-entropy over rows of V logits (f32 or elt in
 // z, overwritten by dZ in the elt type): dZ = (softmax(z) - q) / norm,

@@ -98,7 +98,7 @@ struct BwdWs {
     void* ring[ELT_RING] = {};  // dL/dx in the partition dtype, rotating across layers
     void *dc = nullptr;
     void *dz[2] = {}, *dqkv[2] = {}, *dxq[2] = {}, *dxkv[2] = {};  // by layer parity
-    double *loss_partial = nullptr, *loss_acc = nullptr;
+    double *loss_partial = nullptr, *loss_acc = nullptr;  // partials: loss_rows per micro-batch
     int* flag = nullptr;
     int* bad_label = nullptr;  // set by the cross-entropy head on a label outside [0, V)
     float* splitk = nullptr;   // split-K partial tiles (the call's stream)
@@ -245,9 +245,9 @@ struct gp_partition {
     hipEvent_t unit_ready = nullptr;  // the pair's recompute available (on its first call's stream)
     hipStream_t unit_ready_stream = nullptr;
     unsigned long long unit_ready_capture = 0;
-    Span bwd1_span, splitk1_span, loss1_span, head1_span;
-    // the odd member's loss head done (its loss sum and head gradient come
-    // first; the even member's head waits for it)
+    Span bwd1_span, splitk1_span, head1_span;
+    // the odd member's vocabulary head done (its head gradients come first;
+    // the even member's head waits for it)
     hipEvent_t head_ev = nullptr;
     // Per-layer update: the mini-batch's last backward call records, per layer
     // l, an event on its stream after layer l (every read of layer l's weights
@@ -279,7 +279,8 @@ struct gp_partition {
     bool poison = false;
     std::vector<std::vector<Span>> slot_span; // per set: its residual stream and every buffer of its layer slots
     std::vector<std::vector<Span>> dys_span;  // per member: its rows of every grouped-gradient buffer
-    Span bwd_span, lnpart_span, loss_span, loss_acc_span, head_span;
+    Span bwd_span, lnpart_span, loss_span, loss_acc_span, head_span;  // loss_span: micro-batch 0's partials
+    size_t loss_rows = 0;  // loss partials of one micro-batch
     Span splitk_span[3];                      // caller's stream, weight-gradient stream, recompute stream
     // gp_forward_microbatch_noalloc: this device's address of the static
     // scratch array (nullptr if it could not be resolved) and the most
@@ -350,6 +351,8 @@ struct gp_partition {
     // backward launches them (the lowest member; the others run first and defer)
     int group_size(int m) const { return std::min(group, g.M - (m - m % group)); }
     bool launches_dw(int m) const { return m % group == 0; }
+    // loss partials a micro-batch's head writes (of its loss_rows)
+    int loss_used() const { return g.loss == GP_LOSS_XENT_LS ? xent_partials(g.T()) : loss_blocks(); }
     bool ahead_on = false;  // recompute-ahead / early-recompute stream in use
     bool ahead() const { return ahead_on; }
     void* W(size_t elt_off) const { return welt + elt_off * esz; }
@@ -565,8 +568,10 @@ void plan_workspace(gp_partition* p, Arena& a) {
     }
     size_t lp = (size_t)loss_blocks();
     if (g.loss == GP_LOSS_XENT_LS && (size_t)xent_partials(T) > lp) lp = xent_partials(T);
+    // every micro-batch keeps its partials: the step adds all of them up at once
+    p->loss_rows = lp;
     p->loss_span = Span{a.mark(), lp * sizeof(double)};
-    b.loss_partial = a.take<double>(lp);
+    b.loss_partial = a.take<double>(lp * (g.loss == GP_LOSS_NONE ? 1 : (size_t)g.M));
     p->loss_acc_span = Span{a.mark(), sizeof(double)};
     b.loss_acc = a.take<double>(1);
     b.flag = a.take<int>(1);
@@ -579,13 +584,11 @@ void plan_workspace(gp_partition* p, Arena& a) {
         b.z = a.take_elt(T * (long)g.V, e);
         p->head_span = span_from(h0);
     }
-    // the odd backward lane's loss partials and head scratch; the loss sum and
-    // the flags stay shared (the odd member's head runs first)
-    p->loss1_span = p->head1_span = Span{};
+    // the odd backward lane's head scratch; the loss partials and the flags are shared
+    p->head1_span = Span{};
     if (p->bwd_lanes > 1) {
         BwdWs& q = p->bw1;
-        p->loss1_span = Span{a.mark(), lp * sizeof(double)};
-        q.loss_partial = a.take<double>(lp);
+        q.loss_partial = b.loss_partial;
         q.loss_acc = b.loss_acc;
         q.flag = b.flag;
         q.bad_label = b.bad_label;
@@ -1263,7 +1266,7 @@ gp_status layer_backward(const Ctx& c, int set, int half, int l, bool first, flo
     return GP_OK;
 }
 
-gp_status head_backward(const Ctx& c, int set, bool first, const int* labels, void* dy_elt) {
+gp_status head_backward(const Ctx& c, int set, bool first, const int* labels, void* dy_elt, double* loss_partial) {
     gp_partition* p = c.p;
     const HeadPlan& Hd = p->plan.head;
     BwdWs& b = c.bw ? *c.bw : p->bw;
@@ -1273,8 +1276,7 @@ gp_status head_backward(const Ctx& c, int set, bool first, const int* labels, vo
     GP_TRY(timed_ln_fwd(c, y, T, (int)D, p->master + Hd.lnf.g, p->master + Hd.lnf.b, p->g.eps, b.h, b.sth));
     GP_TRY(linear_fwd(c, Hd.out, b.h, T, b.z, V, EPI_STORE, 0, nullptr, nullptr));
     const double norm = (double)p->g.n * p->g.M * p->g.S;
-    GP_TRY(xent_ls(c.dt, b.z, T, (int)V, labels, p->g.ls, p->g.logit_clip, norm, b.loss_partial, b.bad_label, c.st));
-    GP_TRY(loss_finalize(b.loss_partial, (int)T, b.loss_acc, acc, c.st));
+    GP_TRY(xent_ls(c.dt, b.z, T, (int)V, labels, p->g.ls, p->g.logit_clip, norm, loss_partial, b.bad_label, c.st));
     GP_TRY(linear_dw(c, Hd.out, b.h, b.z, T, acc));
     GP_TRY(linear_dx(c, Hd.out, b.z, T, b.dn, EPI_F32, nullptr, 0));
     return norm_bwd(c, Hd.lnf, b.dn, y, b.sth, T, nullptr, b.p32, dy_elt, acc);
@@ -1839,7 +1841,9 @@ gp_status gp_backward_microbatch_remat(gp_partition* p, int mb, const void* dy_o
         const Span* sk_side = lanes ? nullptr : &p->splitk_span[1];  // lanes: poisoned on the side stream
         const Span* own_bwd = bl ? &p->bwd1_span : &p->bwd_span;
         const Span* own_sk = bl ? &p->splitk1_span : &p->splitk_span[0];
-        const Span* own_loss = bl ? &p->loss1_span : &p->loss_span;
+        const Span mb_loss{p->loss_span.off + (p->g.loss == GP_LOSS_NONE ? 0 : (size_t)mb * p->loss_span.bytes),
+                           p->loss_span.bytes};
+        const Span* own_loss = &mb_loss;
         const Span* own_head = bl ? &p->head1_span : &p->head_span;
         for (const Span* sp : {own_bwd, own_sk, sk_side, own_loss, own_head})
             if (sp) GP_TRY(poison_span(p, *sp, c.st));
@@ -1909,18 +1913,18 @@ gp_status gp_backward_microbatch_remat(gp_partition* p, int mb, const void* dy_o
     const bool pr = p->group > 1;
     const int half = pr ? mb % p->group : 0;
     void* top = pr ? p->off_elt(p->dys[p->d.L - 1].gin, (long)half * T * D) : b.ring[0];
-    // lanes: the loss sum and the head's gradient accumulate in micro-batch order
-    const bool head_order = lanes && p->g.loss != GP_LOSS_NONE;
+    // lanes: the vocabulary head's gradients accumulate in micro-batch order
+    const bool head_order = lanes && p->g.loss == GP_LOSS_XENT_LS;
+    double* loss_partial = b.loss_partial + (p->g.loss == GP_LOSS_NONE ? 0 : (size_t)mb * p->loss_rows);
     if (head_order && !unit_first) GP_HIP(hipStreamWaitEvent(c.st, p->head_ev, 0));
     if (p->g.loss == GP_LOSS_NONE) {
         s = intake(c.dt, dy_or_target, top, b.p32, T * D, c.st);
     } else if (p->g.loss == GP_LOSS_MSE) {
         int nb = 0;
         const double norm = (double)p->g.n * p->g.M * p->g.S * D;
-        s = mse_grad(c.dt, p->xs[set][p->d.L], dy_or_target, T * D, norm, b.p32, top, b.loss_partial, &nb, c.st);
-        if (s == GP_OK) s = loss_finalize(b.loss_partial, nb, b.loss_acc, first ? 0 : 1, c.st);
+        s = mse_grad(c.dt, p->xs[set][p->d.L], dy_or_target, T * D, norm, b.p32, top, loss_partial, &nb, c.st);
     } else {
-        s = head_backward(c, set, first, reinterpret_cast<const int*>(dy_or_target), top);
+        s = head_backward(c, set, first, reinterpret_cast<const int*>(dy_or_target), top, loss_partial);
     }
     if (s != GP_OK) return s;
     if (head_order && record_hi) {
@@ -2123,8 +2127,10 @@ gp_status gp_accumulate_and_step(gp_partition* p, float lr, double* loss_out, gp
     }
     if (loss_out) {
         double v = 0.0;
-        if (p->g.loss != GP_LOSS_NONE)
+        if (p->g.loss != GP_LOSS_NONE) {
+            GP_TRY(loss_finalize(p->bw.loss_partial, (long)p->loss_rows, p->loss_used(), p->g.M, p->bw.loss_acc, st));
             GP_HIP(hipMemcpyAsync(&v, p->bw.loss_acc, sizeof(double), hipMemcpyDeviceToHost, st));
+        }
         GP_HIP(hipStreamSynchronize(st));
         *loss_out = v;
     }
