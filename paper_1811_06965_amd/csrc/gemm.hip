@@ -579,6 +579,18 @@ __device__ __forceinline__ void dl_epilogue_full(const GemmArgs& a, const f32x16
     }
 }
 
+// Ragged K: the lanes whose 16 bytes of the last k-tile (krem deep) lie beyond
+// K move out of range.
+template <int P, int W, bool KM>
+__device__ __forceinline__ void dl_mask(uint32_t* vo, int blk0, int krem, int lane) {
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const int k = KM ? ((lane & 7) ^ swz((blk0 + i) * 8 + (lane >> 3))) * 8
+                         : ((blk0 + i) * 1024 + 16 * lane) / (2 * W);
+        if (k >= krem) vo[i] = OOB;
+    }
+}
+
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16* LdsV4;
 
@@ -591,7 +603,7 @@ __device__ __forceinline__ bf16x8 tr_frag(const char* p, int second) {
     return bf16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
-// Direct-to-LDS GEMM (requires K % 64 == 0).  KM: both operands k-contiguous
+// Direct-to-LDS GEMM.  KM: both operands k-contiguous
 // (A[m lda + k], B[n ldb + k]: forward and input-gradient GEMMs); else both
 // m/n-contiguous (A[k lda + m], B[k ldb + n]: weight-gradient GEMMs, read as
 // the activations are stored).
@@ -619,9 +631,14 @@ __device__ __forceinline__ bf16x8 tr_frag(const char* p, int second) {
 //   hands its accumulators to group 0 through LDS, which adds them and runs
 //   the epilogue.  The k-tile count must be a multiple of KG.
 // F16: A and B hold fp16 values (k-contiguous, no fp4 stage, one k-group).
-template <int BM, int BN, int WM, int WN, int NSTAGE, int EPI, int SM, bool KM, bool MX = false, int KG = 1,
-          bool F16 = false>
-__global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
+// RAG: K is no multiple of 64; the last k-tile's loads beyond K return zeros
+// (one k-group, no fp4 stage).  The register-staged kernel that such reductions
+// fell back to took 8.0 us per 288 x 320 x 1000 GEMM, this 6.7 (with the rest
+// of the layer, in a step).
+// One output tile (tm, tn); under split-K the k-tiles of split `split` of `nsplits`.
+template <int BM, int BN, int WM, int WN, int NSTAGE, int EPI, int SM, bool KM, bool MX, int KG, bool F16, bool RAG>
+__device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int tn, int split, int nsplits) {
+    static_assert(!RAG || (!MX && KG == 1), "ragged K: one k-group, no fp4 stage");
     static_assert(!F16 || (KM && !MX && KG == 1), "fp16 operands: k-contiguous, no fp4 stage, one k-group");
     // SM: 0 no split-K; 1 split-K, partial tiles only (summed by splitk_reduce)
     constexpr bool SPLIT = SM != 0;
@@ -646,23 +663,13 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
     const int kg = wave_all / NW, wave = wave_all % NW;  // k-group, wave within the group
     char* const smem = smem_all + kg * NSTAGE * STAGE;   // the group's stage ring
     const int wm = wave / WN, wn = wave % WN;
-    const int tiles_m = (args.M + BM - 1) / BM, tiles_n = (args.N + BN - 1) / BN;
-    // The band height H of the tile order suits the tiles an XCD runs at once
-    // (P: its 32 CUs times the workgroups that fit a CU): about sqrt(P BN / BM)
-    // rows (a run down whole tile columns would stream all of A through every
-    // XCD; 4 x 8 tiles for 32 workgroups).
-    const int G = gridDim.x;
-    constexpr int RES = (160 * 1024) / (KG * NSTAGE * STAGE) < 1 ? 1 : (160 * 1024) / (KG * NSTAGE * STAGE);
-    const int P = min(max(G >> 3, 1), 32 * min(RES, 3));
-    int tm, tn;
-    band_tile(blockIdx.x, G, tiles_m, tiles_n, P * BN >= 64 * BM ? 8 : 4, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
-    const int nk_all = args.K / BK;
+    const int nk_all = RAG ? (args.K + BK - 1) / BK : args.K / BK;
     int kt0 = 0, kt1 = nk_all;
     if constexpr (SPLIT) {
-        const int per = (nk_all + gridDim.y - 1) / gridDim.y;
-        kt0 = blockIdx.y * per;
+        const int per = (nk_all + nsplits - 1) / nsplits;
+        kt0 = split * per;
         kt1 = min(nk_all, kt0 + per);
     }
     // group-local k-tile i is global k-tile kt0 + i KG + kg
@@ -738,8 +745,18 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
         for (int j = 0; j < TN; ++j)
             scb[j] = __builtin_amdgcn_raw_buffer_load_b8(SB, (uint32_t)(n0 + wn * (BN / WN) + j * 32 + (lane & 31)), 0, 0);
     }
+    const int krem = args.K - (nk_all - 1) * BK;  // RAG: k of the last tile
+#define GP_DL_MASK(t)                                                                        \
+    do {                                                                                     \
+        if constexpr (RAG)                                                                   \
+            if ((t) == nk_all - 1) { /* no load follows this tile's */                       \
+                dl_mask<PA, BM, KM>(voa, wave * PA, krem, lane);                             \
+                dl_mask<PB, BN, KM>(vob, wave * PB, krem, lane);                             \
+            }                                                                                \
+    } while (0)
 #define GP_DL_ISSUE(t, st)                                                                   \
     do {                                                                                     \
+        GP_DL_MASK(t);                                                                       \
         dl_load_blocks<PA>(A, voa, (kt0 + ((t) - kt0) * KG) * ka, (st) + wave * PA * 1024);  \
         dl_load_blocks<PB>(B, vob, (kt0 + ((t) - kt0) * KG) * kb, (st) + BM * 128 + wave * PB * 1024); \
         if constexpr (MX) dl_load_rsrcs<NL4>(R4, vo4, (t) * 32, (st) + STAGE_BF + wave * NL4 * 1024); \
@@ -862,6 +879,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
                     const int cur = s & 1;
                     if constexpr (SPREAD) {
                         // part s of tile i - 1 + NSTAGE, into the stage tile i - 1 left
+                        if (s == 0 && i >= 1 && i - 1 + NSTAGE < nkt) GP_DL_MASK(kt0 + i - 1 + NSTAGE);
                         if (i >= 1 && i - 1 + NSTAGE < nkt)
                             GP_DL_ISSUE_PART(kt0 + i - 1 + NSTAGE, smem + ((st + NSTAGE - 1) % NSTAGE) * STAGE, s);
                     }
@@ -928,6 +946,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
     }
 
 #undef GP_DL_ISSUE
+#undef GP_DL_MASK
 #undef GP_DL_ISSUE_PART
     if constexpr (KG == 2) {
         // group 1 hands its partial sums to group 0 through the (now idle) stage rings;
@@ -965,7 +984,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
                 const int col = col0 + j * 32;
                 if (col < args.N) {
                     if constexpr (SPLIT)
-                        args.ws[((long)gridDim.y * args.M + blockIdx.y) * args.N + col] = cs[j];
+                        args.ws[((long)nsplits * args.M + split) * args.N + col] = cs[j];
                     else
                         args.colsum[col] = args.accumulate ? args.colsum[col] + cs[j] : cs[j];
                 }
@@ -973,7 +992,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
         }
     }
     if constexpr (SPLIT) {
-        const Rsrc ws = make_rsrc(args.ws, (uint32_t)((long)gridDim.y * args.M * args.N * 4));
+        const Rsrc ws = make_rsrc(args.ws, (uint32_t)((long)nsplits * args.M * args.N * 4));
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -983,7 +1002,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
                 for (int r = 0; r < 16; ++r) {
                     const int row = row0 + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
                     const bool ok = row < args.M && col < args.N;
-                    const uint32_t o = ok ? (uint32_t)((((long)blockIdx.y * args.M + row) * args.N + col) * 4) : OOB;
+                    const uint32_t o = ok ? (uint32_t)((((long)split * args.M + row) * args.N + col) * 4) : OOB;
                     const float v = acc[i][j][r];  // see the note in gemm_kernel
                     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ws, o, 0, 0);
                 }
@@ -997,6 +1016,48 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
             ep.template run<TM, TN>(args, acc, row0, col0, lane);
         }
     }
+}
+
+// The band height of a GEMM's tile order suits the tiles an XCD runs at once
+// (its 32 CUs times the workgroups that fit a CU): about sqrt(P BN / BM) rows
+// (a run down whole tile columns would stream all of A through every XCD;
+// 4 x 8 tiles for 32 workgroups).
+template <int BM, int BN, int STAGES>
+__device__ __forceinline__ int band_rows(int grid) {
+    constexpr int RES = (160 * 1024) / (STAGES * (BM + BN) * 128) < 1 ? 1 : (160 * 1024) / (STAGES * (BM + BN) * 128);
+    return min(max(grid >> 3, 1), 32 * min(RES, 3)) * BN >= 64 * BM ? 8 : 4;
+}
+
+template <int BM, int BN, int WM, int WN, int NSTAGE, int EPI, int SM, bool KM, bool MX = false, int KG = 1,
+          bool F16 = false, bool RAG = false>
+__global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
+    int tm, tn;
+    band_tile(xcd_order(blockIdx.x, gridDim.x), (args.M + BM - 1) / BM, (args.N + BN - 1) / BN,
+              band_rows<BM, BN, KG * NSTAGE>(gridDim.x), tm, tn);
+    gemm_dl_tile<BM, BN, WM, WN, NSTAGE, EPI, SM, KM, MX, KG, F16, RAG>(args, tm, tn, blockIdx.y, gridDim.y);
+}
+
+// A layer's weight gradients in one launch: the output tiles of up to
+// MAX_GROUP problems laid end to end (problem i: tiles start[i] .. start[i + 1]).
+// One problem at a time left most of the chip to a few tiles (the o and qkv
+// gradients of a d_model 1024 layer have 64 and 192 tiles, and at d_model 512
+// none has more than 64); together they fill it, in one launch.  (D = 512, F =
+// 2048, 1024 rows: four launches of 21.6 us each, now one.)
+constexpr int MAX_GROUP = 8;
+struct GemmGroup {
+    int n;
+    int start[MAX_GROUP + 1];
+    GemmArgs a[MAX_GROUP];
+};
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool RAG>
+__global__ void __launch_bounds__(64 * WM * WN) gemm_dw_group(GemmGroup g) {
+    const int id = xcd_order(blockIdx.x, gridDim.x);
+    int i = 0;
+    while (i + 1 < g.n && id >= g.start[i + 1]) ++i;
+    const GemmArgs& a = g.a[i];
+    int tm, tn;
+    band_tile(id - g.start[i], (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, band_rows<BM, BN, NSTAGE>(gridDim.x), tm, tn);
+    gemm_dl_tile<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, false, false, 1, false, RAG>(a, tm, tn, 0, 1);
 }
 
 // Sum the split-K partials in split order and apply the epilogue; 4 columns
@@ -1176,13 +1237,13 @@ gp_status launch_tile(const GemmArgs& a, int epi, int splits, hipStream_t st) {
     return GP_OK;
 }
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool KM>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool KM, bool RAG = false>
 gp_status launch_dl(const GemmArgs& a, int epi, int splits, hipStream_t st) {
     constexpr int NT = 64 * WM * WN;
     const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
     if (splits > 1) {
         dim3 grid(tiles, splits);
-        klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_F32, 1, KM>, grid, NT, 0, st, a);
+        klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_F32, 1, KM, false, 1, false, RAG>, grid, NT, 0, st, a);
         GP_LAUNCH_CHECK();
         if (a.deferred && (epi == EPI_RES_F32 || epi == EPI_F32)) {
             *a.deferred = splits;  // the caller reduces
@@ -1192,16 +1253,16 @@ gp_status launch_dl(const GemmArgs& a, int epi, int splits, hipStream_t st) {
     }
     if constexpr (KM) {
         switch (epi) {
-        case EPI_STORE: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_STORE, 0, KM>, tiles, NT, 0, st, a); break;
-        case EPI_RES_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_RES_F32, 0, KM>, tiles, NT, 0, st, a); break;
-        case EPI_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_F32, 0, KM>, tiles, NT, 0, st, a); break;
-        case EPI_RELU_MASK: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_RELU_MASK, 0, KM>, tiles, NT, 0, st, a); break;
-        case EPI_ACC_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, KM>, tiles, NT, 0, st, a); break;
+        case EPI_STORE: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_STORE, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
+        case EPI_RES_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_RES_F32, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
+        case EPI_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_F32, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
+        case EPI_RELU_MASK: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_RELU_MASK, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
+        case EPI_ACC_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
         default: return set_error(GP_ERR_INVALID_ARG, "gemm: epilogue not instantiated for k-contiguous operands");
         }
     } else {
         switch (epi) {
-        case EPI_ACC_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, KM>, tiles, NT, 0, st, a); break;
+        case EPI_ACC_F32: klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, KM, false, 1, false, RAG>, tiles, NT, 0, st, a); break;
         default: return set_error(GP_ERR_INVALID_ARG, "gemm: epilogue not instantiated for m-contiguous operands");
         }
     }
@@ -1300,6 +1361,14 @@ template <bool AK, bool BKM>
 gp_status launch_bf16(const GemmArgs& a, int epi, int cfg, int splits, hipStream_t st) {
     if constexpr (AK == BKM) {
         constexpr bool KM = AK;
+        if (a.K % 64 && cfg > T128x128) {  // decide_bf16 keeps to these shapes
+            if constexpr (KM) {
+                if (cfg == T_DL128x64_S4) return launch_dl<128, 64, 2, 2, 4, KM, true>(a, epi, splits, st);
+                return launch_dl<128, 128, 2, 4, 3, KM, true>(a, epi, splits, st);
+            } else {
+                return launch_dl<128, 128, 2, 4, 2, KM, true>(a, epi, splits, st);
+            }
+        }
         switch (cfg) {
         case T_DL128x128_S2: return launch_dl<128, 128, 2, 2, 2, KM>(a, epi, splits, st);
         case T_DL128x128_S3: return launch_dl<128, 128, 2, 2, 3, KM>(a, epi, splits, st);
@@ -1348,10 +1417,6 @@ gp_status launch_bf16(const GemmArgs& a, int epi, int cfg, int splits, hipStream
 
 constexpr int NUM_CU = 256;
 
-// Pick the tile shape and split count.  Cost = full-machine rounds x per-tile
-// time, where a round holds NUM_CU x (workgroups resident per CU) tiles and
-// co-resident tiles share their CU; per-tile time is the tile's k-steps over
-// a measured relative efficiency; split-K adds its partial-tile traffic.
 // Split-K needs the partial tiles (and, for a fused bias gradient, one row of
 // column sums per split) to fit the workspace, N % 4 == 0 for the reduce, and
 // at least four k-steps per split.
@@ -1360,7 +1425,7 @@ bool split_fits(const GemmArgs& a, int s, int nk) {
     return a.ws != nullptr && nk / s >= 4 && need <= a.ws_elems && a.N % 4 == 0;
 }
 
-// Direct-to-LDS tiles (K % 64 == 0): time = fixed launch cost + rounds x
+// Direct-to-LDS tiles: time = fixed launch cost + rounds x
 // k-steps x per-step time of the tile shape (with the tile running alone on
 // its CU or sharing it with a second one) + the fp32 read-modify-write of an
 // accumulating epilogue + the split-K partial traffic and reduce.  The
@@ -1381,6 +1446,12 @@ double split_weight() {
 }
 
 void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& splits);
+
+// Shapes instantiated for a K that is no multiple of 64 (widths like 1000, odd
+// token counts): one for few output tiles and one for many.
+bool rag_capable(int cfg, bool kmaj) {
+    return kmaj ? cfg == T_DL128x64_S4 || cfg == T_DL128x128_W8S3 : cfg == T_DL128x128_W8A;
+}
 
 // The choice depends only on the problem's shape and operand form; a small
 // per-thread memo (direct-mapped, full key checked) keeps the cost model off
@@ -1432,13 +1503,14 @@ void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& split
     // (partial planes and a reduce) to finish sooner alone, so it is costed
     // three times over for them.
     const double split_w = (kmaj ? 1.0 : 3.0) * split_weight();
-    const int nk = a.K / 64;
+    const int nk = (a.K + 63) / 64;
     double best = 1e300;
     cfg = T_DL128x128_W8A;
     splits = 1;
     for (int ci = 0; ci < ncand; ++ci) {
         const Cand& c = cands[ci];
         if (mx && !mx_capable(c.cfg)) continue;
+        if (a.K % 64 && !rag_capable(c.cfg, kmaj)) continue;
         const long tiles = (long)((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
         for (int s = 1; s <= 4; s *= 2) {
             if (s > 1 && !split_fits(a, s, nk)) continue;
@@ -1451,38 +1523,6 @@ void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& split
             if (t < best * 0.999) {
                 best = t;
                 cfg = c.cfg;
-                splits = s;
-            }
-        }
-    }
-}
-
-void choose(const GemmArgs& a, int epi, int& cfg, int& splits) {
-    static const int BMs[4] = {256, 256, 128, 128}, BNs[4] = {256, 128, 256, 128};
-    static const int resident[4] = {1, 1, 1, 2};
-    static const double eff[4] = {0.95, 0.8, 0.8, 1.0};
-    double best = 1e300;
-    cfg = T128x128;
-    splits = 1;
-    const int nk = (a.K + 63) / 64;
-    for (int c = 0; c < 4; ++c) {
-        const long tiles = (long)((a.M + BMs[c] - 1) / BMs[c]) * ((a.N + BNs[c] - 1) / BNs[c]);
-        for (int s = 1; s <= 8; s *= 2) {
-            if (s > 1 && !split_fits(a, s, nk)) continue;
-            const long wgs = tiles * s;
-            const long slots = (long)NUM_CU * resident[c];
-            const long rounds = (wgs + slots - 1) / slots;
-            const long per_cu = std::min<long>(resident[c], (wgs + NUM_CU - 1) / NUM_CU);
-            const double kt = (double)((nk + s - 1) / s);
-            // time in units of one 128x128x64 tile step of a CU running alone
-            // two co-resident tiles hide each other's latencies: 1.5x, not 2x, the time of one
-            double t = rounds * (per_cu == 2 ? 1.5 : 1.0) * (BMs[c] / 128.0) * (BNs[c] / 128.0) * kt / eff[c];
-            // split-K: partial-tile traffic at ~1.75 TB/s and the reduce launch (one
-            // unit = one 128x128x64 step of a lone tile, ~0.58 us on MI355X)
-            if (s > 1) t += (double)a.M * a.N * 4.0 * (s + 1.0) / 2.0 / 1.0e6 + 4.0;
-            if (t < best * 0.999) {
-                best = t;
-                cfg = c;
                 splits = s;
             }
         }
@@ -1524,16 +1564,13 @@ void decide_bf16(const GemmArgs& args, int epi, bool a_kmajor, int& cfg, int& sp
         }
         return;
     }
-    if (a.K % 64 == 0)
-        choose_dl(a, epi, a_kmajor, cfg, splits);
-    else
-        choose(a, epi, cfg, splits);
+    choose_dl(a, epi, a_kmajor, cfg, splits);
     if (a.force_cfg >= 0 && a.force_cfg <= T_LAST) {
         cfg = a.force_cfg;
         splits = a.force_splits > 0 ? a.force_splits : 1;
         if (splits > 1 && !split_fits(a, splits, (a.K + 63) / 64)) splits = 1;
     }
-    if (cfg > T128x128 && a.K % 64) cfg = T128x128;
+    if (cfg > T128x128 && a.K % 64 && !rag_capable(cfg, a_kmajor)) cfg = a_kmajor ? T_DL128x128_W8S3 : T_DL128x128_W8A;
     const bool narrow = cfg == T_DL128x64 || cfg == T_DL64x128 || cfg == T_DL128x64_S3 || cfg == T_DL128x64_S4;
     const bool kg2 = cfg == T_DL128x64_KG2 || cfg == T_DL128x128_KG2 || cfg == T_DL64x128_KG2;
     if (!a_kmajor && (narrow || kg2)) cfg = T_DL128x128_W8A;  // no 64-wide or k-group m-contiguous tiles
@@ -1549,6 +1586,27 @@ long gemm_workspace_need(const GemmArgs& a, int epi, bool a_kmajor, int dtype) {
     int cfg = 0, splits = 1;
     decide_bf16(a, epi, a_kmajor, cfg, splits);
     return splits > 1 ? (long)splits * a.M * a.N + (a.colsum ? (long)splits * a.N : 0) : 0;
+}
+
+gp_status gemm_dw_group(const GemmArgs* a, int n, hipStream_t st) {
+    if (n < 1 || n > MAX_GROUP) return set_error(GP_ERR_INVALID_ARG, "gemm group: problem count");
+    GemmGroup g;
+    g.n = n;
+    g.start[0] = 0;
+    bool rag = false;
+    for (int i = 0; i < n; ++i) {
+        gp_status s = check_args<bf16>(a[i], false, false);
+        if (s != GP_OK) return s;
+        g.a[i] = a[i];
+        g.start[i + 1] = g.start[i] + ((a[i].M + 127) / 128) * ((a[i].N + 127) / 128);
+        rag = rag || a[i].K % 64;
+    }
+    if (rag)
+        klaunch(gemm_dw_group<128, 128, 2, 4, 2, true>, g.start[n], 512, 0, st, g);
+    else
+        klaunch(gemm_dw_group<128, 128, 2, 4, 2, false>, g.start[n], 512, 0, st, g);
+    GP_LAUNCH_CHECK();
+    return GP_OK;
 }
 
 gp_status gemm(const GemmArgs& a, int epi, bool a_kmajor, bool b_kmajor, int dtype, hipStream_t st) {

@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(GemmArgs args) {
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform_wave_id(tid);
     const int wm = wave / WN, wn = wave % WN, fr = lane & (BLK - 1);
     int tm, tn;
-    band_tile(blockIdx.x, gridDim.x, (args.M + BM - 1) / BM, (args.N + BN - 1) / BN, 8, tm, tn);
+    band_tile(xcd_order(blockIdx.x, gridDim.x), (args.M + BM - 1) / BM, (args.N + BN - 1) / BN, 8, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int K = args.K, nk = (K + BK - 1) / BK;
 

@@ -43,16 +43,18 @@ __device__ __forceinline__ void lds_barrier() {
 // from it stay in SGPRs (M0 of the direct loads).
 __device__ __forceinline__ int uniform_wave_id(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
 
-// Output tile of workgroup `bid` of a grid of G workgroups (bid < G).
-// Consecutive workgroup ids go round-robin to the 8 XCDs, so ids are first
-// regrouped into one contiguous run per XCD; tiles are then numbered in bands
-// of H tile rows, column by column within a band, so that the tiles one XCD
-// runs at a time form a compact block and its L2 serves each A row panel and
-// B column panel to several of them.
-__device__ __forceinline__ void band_tile(int bid, int G, int tiles_m, int tiles_n, int H, int& tm, int& tn) {
+// Consecutive workgroup ids go round-robin to the 8 XCDs: regrouped into one
+// contiguous run of ids per XCD (bid < G, the grid).
+__device__ __forceinline__ int xcd_order(int bid, int G) {
     const int G8 = G & ~7;
-    if (bid < G8) bid = (bid & 7) * (G8 >> 3) + (bid >> 3);
-    const int band = bid / (H * tiles_n), in_band = bid - band * H * tiles_n;
+    return bid < G8 ? (bid & 7) * (G8 >> 3) + (bid >> 3) : bid;
+}
+// Output tile `id` of a problem: tiles are numbered in bands of H tile rows,
+// column by column within a band, so that the tiles one XCD runs at once form
+// a compact block and its L2 serves each A row panel and B column panel to
+// several of them.
+__device__ __forceinline__ void band_tile(int id, int tiles_m, int tiles_n, int H, int& tm, int& tn) {
+    const int band = id / (H * tiles_n), in_band = id - band * H * tiles_n;
     const int bh = min(H, tiles_m - band * H);
     tm = band * H + in_band % bh;
     tn = in_band / bh;

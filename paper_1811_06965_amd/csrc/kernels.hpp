@@ -58,6 +58,9 @@ struct GemmArgs {
 };
 
 gp_status gemm(const GemmArgs& a, int epi, bool a_kmajor, bool b_kmajor, int dtype, hipStream_t st);
+// n (<= 8) bf16 weight-gradient GEMMs (EPI_ACC_F32, m/n-contiguous operands,
+// column sums as asked for) in one launch; no split-K.
+gp_status gemm_dw_group(const GemmArgs* a, int n, hipStream_t st);
 // The fp32 GEMM (gemm_f32.hip), operands of one majorness (k_major: both
 // k-contiguous); no split-K: ws is not used.  Arguments checked by gemm().
 gp_status gemm_f32(const GemmArgs& a, int epi, bool k_major, hipStream_t st);
