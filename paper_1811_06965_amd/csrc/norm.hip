@@ -389,6 +389,115 @@ __global__ void __launch_bounds__(256) ln_bwd_v4(const float* __restrict__ dn, c
     }
 }
 
+// The LayerNorm backward for wide rows: the block's 256 threads share a row
+// (thread t owns float4 chunks t + 256 c), two rows at a time, with the row
+// sums exchanged through 128 bytes of LDS per pair; a thread keeps its
+// features' parameter sums for the block's rows (the same 4 rpw rows as
+// ln_bwd_v4, summed in row order).  ln_bwd_v4's wave per row takes 469 VGPRs
+// and 64 KB of LDS at D = 2048, so that beside a weight-gradient or recompute
+// GEMM it waits for a whole CU to drain: 109 us per launch in a step at 1024
+// rows of 2048, 58 in this form (floor 8), and the step of one d_model 2048
+// layer 30.0 -> 29.1 ms.  At D = 1024 (226 VGPRs, 32 KB) the 2-layer decoder
+// 19.7 -> 19.3 ms and the 16-layer encoder 65.1 -> 64.2; narrower rows keep the
+// wave per row.
+template <typename T, int CW>
+__global__ void __launch_bounds__(256) ln_bwd_wide(const float* __restrict__ dn, const float* __restrict__ x,
+                                                   const float* __restrict__ stats, const float* __restrict__ gamma,
+                                                   long rows, int D, int rpw, const float* __restrict__ dres,
+                                                   float* __restrict__ dx32, T* __restrict__ dxe,
+                                                   float* __restrict__ partial, int accumulate, int dn_splits,
+                                                   long dn_plane) {
+    __shared__ float red[2][2][4][2];  // [parity of the pair][row][wave][sum]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n4 = D / 4;
+    const f32x4* g4 = reinterpret_cast<const f32x4*>(gamma);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 pg[CW], pb[CW], gm[CW];
+#pragma unroll
+    for (int c = 0; c < CW; ++c) {
+        pg[c] = pb[c] = zero;
+        gm[c] = tid + 256 * c < n4 ? g4[tid + 256 * c] : zero;
+    }
+    const long row0 = (long)blockIdx.x * LN_WAVES * rpw, end = min(rows, row0 + (long)LN_WAVES * rpw);
+    int par = 0;
+    for (long row = row0; row < end; row += 2, par ^= 1) {
+        f32x4 dv[2][CW], xh[2][CW], rv[2][CW];
+        float mu[2], rstd[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const bool live = row + r < end;
+            const long o = live ? row + r : row;
+            mu[r] = stats[2 * o];
+            rstd[r] = stats[2 * o + 1];
+            const f32x4* dn4 = reinterpret_cast<const f32x4*>(dn + o * D);
+            const f32x4* x4 = reinterpret_cast<const f32x4*>(x + o * D);
+            const f32x4* r4 = reinterpret_cast<const f32x4*>(dres + o * D);
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const int i = tid + 256 * c;
+                dv[r][c] = xh[r][c] = rv[r][c] = zero;
+                if (i >= n4 || !live) continue;
+                dv[r][c] = dn4[i];
+                for (int k = 1; k < dn_splits; ++k) dv[r][c] += dn4[i + k * (dn_plane / 4)];
+                xh[r][c] = x4[i];
+                if (dres) rv[r][c] = r4[i];
+            }
+        }
+        float s[2][2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            s[r][0] = s[r][1] = 0.f;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                if (tid + 256 * c >= n4) continue;
+                xh[r][c] = (xh[r][c] - mu[r]) * rstd[r];
+                const f32x4 g = dv[r][c] * gm[c];
+                if (row + r < end) {
+                    pg[c] += dv[r][c] * xh[r][c];
+                    pb[c] += dv[r][c];
+                }
+                s[r][0] += hsum(g);
+                s[r][1] += hsum(g * xh[r][c]);
+            }
+            s[r][0] = wave_sum(s[r][0]);
+            s[r][1] = wave_sum(s[r][1]);
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                red[par][r][wave][0] = s[r][0];
+                red[par][r][wave][1] = s[r][1];
+            }
+        }
+        __syncthreads();  // one per pair: the other parity's sums were read before this one's barrier
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (row + r >= end) break;
+            const float sg = ((red[par][r][0][0] + red[par][r][1][0]) + (red[par][r][2][0] + red[par][r][3][0])) / D;
+            const float sgx = ((red[par][r][0][1] + red[par][r][1][1]) + (red[par][r][2][1] + red[par][r][3][1])) / D;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const int i = tid + 256 * c;
+                if (i >= n4) continue;
+                const f32x4 v = rstd[r] * (dv[r][c] * gm[c] - sg - xh[r][c] * sgx) + rv[r][c];
+                if (dx32) reinterpret_cast<f32x4*>(dx32 + (row + r) * D)[i] = v;
+                if (dxe) Out4<T>::store(dxe + (row + r) * D + 4 * i, v);
+            }
+        }
+    }
+    f32x4* pp = reinterpret_cast<f32x4*>(partial + (long)blockIdx.x * 2 * D);
+#pragma unroll
+    for (int c = 0; c < CW; ++c) {
+        const int i = tid + 256 * c;
+        if (i >= n4) continue;
+        if (accumulate) {
+            pg[c] += pp[i];
+            pb[c] += pp[n4 + i];
+        }
+        pp[i] = pg[c];
+        pp[n4 + i] = pb[c];
+    }
+}
+
 template <typename T>
 gp_status ln_fwd_t(const float* x, long rows, int D, const float* g, const float* b, float eps, void* out,
                    float* stats, unsigned char* lo4, unsigned char* lo_sc, _Float16* o16, hipStream_t st) {
@@ -435,11 +544,14 @@ gp_status ln_bwd_t(const float* dn, const float* x, const float* stats, const fl
         case 1: GP_LNV(1); break;
         case 2: GP_LNV(2); break;
         case 3: GP_LNV(3); break;
-        case 4: GP_LNV(4); break;
-        case 5: GP_LNV(5); break;
-        case 6: GP_LNV(6); break;
-        case 7: GP_LNV(7); break;
-        default: GP_LNV(8); break;
+        case 4:
+            klaunch(ln_bwd_wide<T, 1>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e,
+                    partial, accumulate, dn_splits, dn_plane);
+            break;
+        default:
+            klaunch(ln_bwd_wide<T, 2>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e,
+                    partial, accumulate, dn_splits, dn_plane);
+            break;
         }
 #undef GP_LNV
         GP_LAUNCH_CHECK();

@@ -59,3 +59,14 @@ def test_f32_gemm_tiles_agree_bit_for_bit(name, monkeypatch):
         for a, b in zip(r["grads"] + [r["head"]], res[0]["grads"] + [res[0]["head"]]):
             for k in a:
                 assert np.array_equal(a[k], b[k]), k
+
+
+# the block-per-row LayerNorm backward: one, two and a partial second chunk per
+# thread; several rows per block (2052 rows: rows per wave 2, a short last block)
+@pytest.mark.parametrize("d_model,heads,seq,batch,micro", [(1024, 16, 513, 4, 1), (1280, 20, 12, 2, 2),
+                                                           (1792, 28, 20, 1, 1), (2048, 32, 8, 3, 3)])
+def test_layernorm_backward_of_wide_rows(d_model, heads, seq, batch, micro):
+    cfg = synth.PartitionConfig("wide", layers=1, d_model=d_model, d_ff=64, heads=heads, seq=seq, batch=batch,
+                                micro=micro, dtype="f32", loss="mse")
+    case = synth.make_case(cfg, 4, perturb=True)
+    _against_oracle(cfg, case, _step(cfg, case))
