@@ -37,8 +37,8 @@
 
 namespace gp {
 
-gp_status attention_fwd_simt(int dtype, const AttnArgs& a, hipStream_t st);
-gp_status attention_bwd_simt(int dtype, const AttnArgs& a, hipStream_t st);
+gp_status attention_fwd_f32(const AttnArgs& a, hipStream_t st);
+gp_status attention_bwd_f32(const AttnArgs& a, hipStream_t st);
 
 namespace {
 
@@ -776,7 +776,7 @@ bool mfma_ok(const AttnArgs& a) {
 } // namespace
 
 gp_status attention_fwd(int dtype, const AttnArgs& a, hipStream_t st) {
-    if (dtype != GP_BF16) return attention_fwd_simt(dtype, a, st);
+    if (dtype != GP_BF16) return attention_fwd_f32(a, st);
     if (!mfma_ok(a)) return set_error(GP_ERR_UNSUPPORTED, "bf16 attention needs d_h = 64 and lengths multiple of 32, <= 256");
     const int w = waves_for(a, (long)(a.Sq / 32) * (a.hint_n ? a.hint_n : a.n) * a.H);
     dim3 grid((a.Sq + 32 * w - 1) / (32 * w), a.n * a.H);
@@ -790,7 +790,7 @@ gp_status attention_fwd(int dtype, const AttnArgs& a, hipStream_t st) {
 }
 
 gp_status attention_bwd(int dtype, const AttnArgs& a, hipStream_t st) {
-    if (dtype != GP_BF16) return attention_bwd_simt(dtype, a, st);
+    if (dtype != GP_BF16) return attention_bwd_f32(a, st);
     if (!mfma_ok(a)) return set_error(GP_ERR_UNSUPPORTED, "bf16 attention needs d_h = 64 and lengths multiple of 32, <= 256");
     const int wq = waves_for(a, (long)(a.Sq / 32) * (a.hint_n ? a.hint_n : a.n) * a.H);
     dim3 gq((a.Sq + 32 * wq - 1) / (32 * wq), a.n * a.H);

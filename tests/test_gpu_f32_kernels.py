@@ -70,3 +70,19 @@ def test_layernorm_backward_of_wide_rows(d_model, heads, seq, batch, micro):
                                 micro=micro, dtype="f32", loss="mse")
     case = synth.make_case(cfg, 4, perturb=True)
     _against_oracle(cfg, case, _step(cfg, case))
+
+
+# 16-row blocks with remainders, score rows of each length class (up to 128,
+# 320 and 1024 columns) and their edges, head widths of one to four 16-column
+# blocks with remainders; causal self-attention and cross-attention of another
+# length (at least two keys: over one the query gradients are zero and have no relative error)
+@pytest.mark.parametrize("heads,dh,seq,mem_seq", [(2, 64, 16, 0), (3, 4, 20, 0), (2, 20, 132, 0), (1, 48, 320, 0),
+                                                  (1, 36, 324, 0), (2, 64, 17, 129), (2, 12, 128, 2),
+                                                  (1, 40, 1024, 3)])
+def test_f32_attention_lengths_and_widths(heads, dh, seq, mem_seq):
+    dec = mem_seq > 0
+    cfg = synth.PartitionConfig("attn", layers=1, d_model=heads * dh * (1 if heads * dh % 8 == 0 else 2), d_ff=64,
+                                heads=heads * (1 if heads * dh % 8 == 0 else 2), seq=seq, mem_seq=mem_seq, batch=4,
+                                micro=1, dtype="f32", kind="decoder" if dec else "encoder", loss="mse")
+    case = synth.make_case(cfg, 6, perturb=True)
+    _against_oracle(cfg, case, _step(cfg, case))
