@@ -153,14 +153,9 @@ gp_status xent_ls(int dtype, void* z, long rows, int V, const int* labels, float
 int xent_partials(long rows);
 
 // --------------------------------------------------------------- update
-// w[i] -= lr * g[i] for i < count (fp32 masters).
 // Sustained bf16 MFMA rate of a register-only 32x32x16 loop on every CU
 // (best of three timed runs after one warm-up), in TFLOP/s; synchronises st.
 gp_status mfma_peak(hipStream_t st, double* tflops);
-gp_status sgd_update(float* w, const float* g, float lr, long count, hipStream_t st);
-// ms = rho ms + (1 - rho) g^2;  w -= lr g / sqrt(ms + eps)  (count % 4 == 0, 16-byte aligned).
-gp_status rmsprop_update(float* w, const float* g, float* ms, float lr, float rho, float eps, long count,
-                         hipStream_t st);
 // Working copies of one linear layer from its fp32 master W [in, out], in the
 // partition dtype: kn = W [in, out], nk = W^T [out, in].  q4 / q4s (optional,
 // bf16): the rows of nk in fp4 [out, in/2] bytes with one E8M0 scale per row
@@ -168,15 +163,22 @@ gp_status rmsprop_update(float* w, const float* g, float* ms, float lr, float rh
 // instead (the B operand of a GEMM with fp16 operands, GemmArgs::f16).
 gp_status refresh_linear(int dtype, const float* w, int in, int out, void* kn, void* nk, void* q4, void* q4s,
                          hipStream_t st, bool nk16 = false);
-// The SGD (ms == nullptr) or RMSProp step of a linear's fp32 weights fused
-// with the refresh of its bf16 working copies as refresh_linear makes them;
-// in, out multiples of 64.
-gp_status update_refresh_linear(float* w, const float* g, float* ms, float lr, float rho, float eps, int in,
-                                int out, void* kn, void* nk, void* q4, void* q4s, hipStream_t st, bool nk16 = false);
-// The same update over nranges float ranges (offset, count pairs in device
-// memory), one workgroup each.
-gp_status update_ranges(float* w, const float* g, float* ms, float lr, float rho, float eps, const long* ranges,
-                        int nranges, hipStream_t st);
+// The rows of nk [out, in] (bf16) in fp4, as refresh_linear's q4 / q4s.
+gp_status quantize_rows_fp4(const void* nk, int out, int in, void* q4, void* q4s, hipStream_t st);
+// A linear of the update's table (device memory): its float offset in master /
+// grads / ms, the element offsets of its working copies, and the number of 64 x
+// 64 tiles of the linears before it.
+struct UpdateLinear {
+    long w, kn, nk;
+    int in, out, tile0, nk16;
+};
+// The SGD (ms == nullptr) or RMSProp step of linears l0 .. l1 - 1 (`tiles` tiles)
+// fused with the refresh of their working copies as refresh_linear makes them
+// (fp4 copies excepted), and of nranges float ranges (offset, count pairs in
+// device memory): one launch.
+gp_status update_linears(int dtype, float* master, const float* grads, float* ms, float lr, float rho, float eps,
+                         void* welt, const UpdateLinear* table, int l0, int l1, int tiles, const long* ranges,
+                         int nranges, hipStream_t st);
 // An empty launch labelled by its grid (role x (edge + 1) workgroups of one
 // wave): edge 0 before, 1 after a timed launch, so that per-dispatch profiler
 // records can be attributed to launch roles.

@@ -238,30 +238,6 @@ __global__ void __launch_bounds__(256) xent_rows_kernel(bf16* __restrict__ z, in
     if (tid == 0) partial[row] = ((double)(m + logf(se)) - (double)u * sz - (1.0 - ls) * zl) / norm;
 }
 
-__global__ void __launch_bounds__(256) sgd_kernel(float* __restrict__ w, const float* __restrict__ g, float lr,
-                                                  long count) {
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long)gridDim.x * 256) w[i] -= lr * g[i];
-}
-
-// RMSProp: ms <- rho ms + (1 - rho) g^2;  w <- w - lr g / sqrt(ms + eps).
-// Four parameters per thread with 16-byte accesses (count % 4 == 0: every
-// parameter block of the plan is 64-float aligned).
-__global__ void __launch_bounds__(256) rmsprop_kernel(f32x4* __restrict__ w, const f32x4* __restrict__ g,
-                                                      f32x4* __restrict__ ms, float lr, float rho, float eps,
-                                                      long n4) {
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long)gridDim.x * 256) {
-        const f32x4 gv = g[i];
-        f32x4 m = ms[i], wv = w[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            m[e] = rho * m[e] + (1.f - rho) * (gv[e] * gv[e]);
-            wv[e] -= lr * gv[e] / sqrtf(m[e] + eps);
-        }
-        ms[i] = m;
-        w[i] = wv;
-    }
-}
-
 // kn = W, nk = W^T through a 64 x 64 LDS tile (both writes coalesced).
 template <typename T>
 __global__ void __launch_bounds__(256) refresh_kernel(const float* __restrict__ w, int in, int out,
@@ -298,6 +274,12 @@ template <> struct Copy4<_Float16> {
     }
 };
 
+template <> struct Copy4<float> {
+    static __device__ __forceinline__ void store(float* p, float a, float b, float c, float d) {
+        *reinterpret_cast<f32x4*>(p) = {a, b, c, d};
+    }
+};
+
 // The same for bf16 copies of whole 64 x 64 tiles (in, out multiples of 64):
 // 16-byte reads of W, 8-byte writes of both copies.  NK: the element type of
 // the transposed copy (bf16, or fp16 for a GEMM with fp16 operands).
@@ -323,67 +305,111 @@ __global__ void __launch_bounds__(256) refresh_bf16_tiles(const float* __restric
     }
 }
 
-// The update of a linear's weights fused with the refresh of its bf16 working
-// copies (in, out multiples of 64): W <- W - lr G (SGD) or the RMSProp step
-// (rms: ms <- rho ms + (1 - rho) G^2; W <- W - lr G / sqrt(ms + eps)) on the
-// fp32 master, then kn = W, nk = W^T from the updated values through a
-// 64 x 64 LDS tile -- one pass over W and G instead of an update pass and a
-// refresh pass.  Per element the same arithmetic as sgd_kernel and
-// rmsprop_kernel.
-template <typename NK>
-__global__ void __launch_bounds__(256) update_refresh_tiles(float* __restrict__ w, const float* __restrict__ g,
-                                                            float* __restrict__ ms, float lr, float rho, float eps,
-                                                            int rms, int in, int out, bf16* __restrict__ kn,
-                                                            NK* __restrict__ nk) {
-    __shared__ float tile[64][65];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64, t = threadIdx.x;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int idx = t + 256 * k, r = idx >> 4, c = (idx & 15) * 4;
-        const long o = (long)(r0 + r) * out + c0 + c;
-        f32x4 v = *reinterpret_cast<const f32x4*>(w + o);
-        const f32x4 gv = *reinterpret_cast<const f32x4*>(g + o);
-        if (rms) {
-            f32x4 m = *reinterpret_cast<const f32x4*>(ms + o);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                m[e] = rho * m[e] + (1.f - rho) * (gv[e] * gv[e]);
-                v[e] -= lr * gv[e] / sqrtf(m[e] + eps);
-            }
-            *reinterpret_cast<f32x4*>(ms + o) = m;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] -= lr * gv[e];
-        }
-        *reinterpret_cast<f32x4*>(w + o) = v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) tile[r][c + j] = v[j];
-        *reinterpret_cast<bf16x4*>(kn + o) = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+// W <- W - lr G (SGD), or the RMSProp step (rms: ms <- rho ms + (1 - rho) G^2;
+// W <- W - lr G / sqrt(ms + eps)), of one parameter.
+__device__ __forceinline__ float update_one(float w, float g, float& m, float lr, float rho, float eps, int rms) {
+    if (rms) {
+        m = rho * m + (1.f - rho) * (g * g);
+        w -= lr * g / sqrtf(m + eps);
+    } else {
+        w -= lr * g;
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int idx = t + 256 * k, c = idx >> 4, r = (idx & 15) * 4;
-        Copy4<NK>::store(nk + (long)(c0 + c) * in + r0 + r, tile[r][c], tile[r + 1][c], tile[r + 2][c], tile[r + 3][c]);
-    }
+    return w;
 }
 
-// The same update over the parameters outside the linears' weight blocks
-// (biases, LayerNorm gains and shifts): workgroup b takes the float range
-// [ranges[2 b], ranges[2 b] + ranges[2 b + 1]).
-__global__ void __launch_bounds__(256) update_ranges_kernel(float* __restrict__ w, const float* __restrict__ g,
-                                                            float* __restrict__ ms, float lr, float rho, float eps,
-                                                            int rms, const long* __restrict__ ranges) {
-    const long off = ranges[2 * blockIdx.x], n = ranges[2 * blockIdx.x + 1];
-    for (long i = off + threadIdx.x; i < off + n; i += 256) {
-        const float gv = g[i];
-        if (rms) {
-            const float m = rho * ms[i] + (1.f - rho) * (gv * gv);
-            ms[i] = m;
-            w[i] -= lr * gv / sqrtf(m + eps);
-        } else {
-            w[i] -= lr * gv;
+// The update of linears l0 .. l1 - 1 of the table, fused with the refresh of
+// their working copies: a workgroup per 64 x 64 tile of W (tiles of the table's
+// linears end to end, from linear l0's first) reads W and G once and writes W,
+// the copy kn and, through an LDS tile, the transposed copy nk; 16-byte accesses
+// where in and out are multiples of 64.  Workgroups from `tiles` on update the
+// parameters outside the weights: workgroup tiles + r the float range r.
+// Bound by HBM for large layers (16 bytes per weight with SGD, 12 with fp32
+// copies); for small ones by the launches, which one per linear, plus one for
+// the rest, cost 5 us of host time each: the smallest fp32 step 1085 -> 959 us,
+// two ragged layers 1495 -> 1361.
+template <typename T>
+__global__ void __launch_bounds__(256) update_kernel(float* __restrict__ master, const float* __restrict__ grads,
+                                                     float* __restrict__ ms, float lr, float rho, float eps, int rms,
+                                                     T* __restrict__ welt, const UpdateLinear* __restrict__ tab, int l0,
+                                                     int l1, int tiles, const long* __restrict__ ranges) {
+    __shared__ float tile[64][65];
+    const int t = threadIdx.x;
+    if ((int)blockIdx.x >= tiles) {
+        const long r = blockIdx.x - tiles, off = ranges[2 * r], n = ranges[2 * r + 1];
+        for (long i = off + t; i < off + n; i += 256) {
+            float m = rms ? ms[i] : 0.f;
+            master[i] = update_one(master[i], grads[i], m, lr, rho, eps, rms);
+            if (rms) ms[i] = m;
         }
+        return;
+    }
+    const int id = tab[l0].tile0 + blockIdx.x;
+    int l = l0;
+    for (int hi = l1; l + 1 < hi;) {  // the last linear whose first tile is not after id
+        const int mid = (l + hi) / 2;
+        if (tab[mid].tile0 <= id)
+            l = mid;
+        else
+            hi = mid;
+    }
+    const UpdateLinear u = tab[l];
+    const int nx = (u.out + 63) / 64, k0 = id - u.tile0, r0 = k0 / nx * 64, c0 = k0 % nx * 64;
+    float* w = master + u.w;
+    const float* g = grads + u.w;
+    float* mm = ms + u.w;
+    T* kn = welt + u.kn;
+    T* nk = welt + u.nk;
+    if (u.in % 64 == 0 && u.out % 64 == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int idx = t + 256 * k, r = idx >> 4, c = (idx & 15) * 4;
+            const long o = (long)(r0 + r) * u.out + c0 + c;
+            f32x4 v = *reinterpret_cast<const f32x4*>(w + o);
+            const f32x4 gv = *reinterpret_cast<const f32x4*>(g + o);
+            f32x4 m = {0.f, 0.f, 0.f, 0.f};
+            if (rms) m = *reinterpret_cast<const f32x4*>(mm + o);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float me = m[e];
+                v[e] = update_one(v[e], gv[e], me, lr, rho, eps, rms);
+                m[e] = me;
+            }
+            if (rms) *reinterpret_cast<f32x4*>(mm + o) = m;
+            *reinterpret_cast<f32x4*>(w + o) = v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) tile[r][c + j] = v[j];
+            Copy4<T>::store(kn + o, v[0], v[1], v[2], v[3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int idx = t + 256 * k, c = idx >> 4, r = (idx & 15) * 4;
+            const long o = (long)(c0 + c) * u.in + r0 + r;
+            if (u.nk16)  // fp16 in place of the partition's 16-bit type
+                Copy4<_Float16>::store(reinterpret_cast<_Float16*>(nk) + o, tile[r][c], tile[r + 1][c], tile[r + 2][c],
+                                       tile[r + 3][c]);
+            else
+                Copy4<T>::store(nk + o, tile[r][c], tile[r + 1][c], tile[r + 2][c], tile[r + 3][c]);
+        }
+        return;
+    }
+    const int tx = t & 63, ty = t >> 6;
+    for (int r = ty; r < 64; r += 4) {
+        const int row = r0 + r, col = c0 + tx;
+        if (row < u.in && col < u.out) {
+            const long o = (long)row * u.out + col;
+            float m = rms ? mm[o] : 0.f;
+            const float v = update_one(w[o], g[o], m, lr, rho, eps, rms);
+            if (rms) mm[o] = m;
+            w[o] = v;
+            tile[r][tx] = v;
+            kn[o] = to_elt<T>(v);
+        }
+    }
+    __syncthreads();
+    for (int c = ty; c < 64; c += 4) {
+        const int col = c0 + c, row = r0 + tx;
+        if (row < u.in && col < u.out) nk[(long)col * u.in + row] = to_elt<T>(tile[tx][c]);
     }
 }
 
@@ -565,46 +591,24 @@ gp_status mfma_peak(hipStream_t st, double* tflops) {
     return s;
 }
 
-gp_status sgd_update(float* w, const float* g, float lr, long count, hipStream_t st) {
-    klaunch(sgd_kernel, ew_grid(count), 256, 0, st, w, g, lr, count);
-    GP_LAUNCH_CHECK();
-    return GP_OK;
-}
-
-gp_status rmsprop_update(float* w, const float* g, float* ms, float lr, float rho, float eps, long count,
-                         hipStream_t st) {
-    if (count % 4) return set_error(GP_ERR_INVALID_ARG, "rmsprop: parameter count must be a multiple of 4");
-    klaunch(rmsprop_kernel, ew_grid(count / 4), 256, 0, st, reinterpret_cast<f32x4*>(w),
-            reinterpret_cast<const f32x4*>(g), reinterpret_cast<f32x4*>(ms), lr, rho, eps, count / 4);
-    GP_LAUNCH_CHECK();
-    return GP_OK;
-}
-
-gp_status update_refresh_linear(float* w, const float* g, float* ms, float lr, float rho, float eps, int in,
-                                int out, void* kn, void* nk, void* q4, void* q4s, hipStream_t st, bool nk16) {
-    if (in % 64 || out % 64) return set_error(GP_ERR_INVALID_ARG, "update_refresh: in and out must be multiples of 64");
-    if (nk16 && q4) return set_error(GP_ERR_INVALID_ARG, "update_refresh: an fp16 W^T has no fp4 copy");
-    dim3 grid(out / 64, in / 64);
-    if (nk16)
-        klaunch(update_refresh_tiles<_Float16>, grid, 256, 0, st, w, g, ms, lr, rho, eps, ms ? 1 : 0, in, out,
-                reinterpret_cast<bf16*>(kn), reinterpret_cast<_Float16*>(nk));
+gp_status update_linears(int dtype, float* master, const float* grads, float* ms, float lr, float rho, float eps,
+                         void* welt, const UpdateLinear* table, int l0, int l1, int tiles, const long* ranges,
+                         int nranges, hipStream_t st) {
+    if (tiles + nranges <= 0) return GP_OK;
+    if (dtype == GP_BF16)
+        klaunch(update_kernel<bf16>, tiles + nranges, 256, 0, st, master, grads, ms, lr, rho, eps, ms ? 1 : 0,
+                static_cast<bf16*>(welt), table, l0, l1, tiles, ranges);
     else
-        klaunch(update_refresh_tiles<bf16>, grid, 256, 0, st, w, g, ms, lr, rho, eps, ms ? 1 : 0, in, out,
-                reinterpret_cast<bf16*>(kn), reinterpret_cast<bf16*>(nk));
+        klaunch(update_kernel<float>, tiles + nranges, 256, 0, st, master, grads, ms, lr, rho, eps, ms ? 1 : 0,
+                static_cast<float*>(welt), table, l0, l1, tiles, ranges);
     GP_LAUNCH_CHECK();
-    if (q4) {
-        if (in % 8) return set_error(GP_ERR_UNSUPPORTED, "refresh: fp4 copies are made from bf16 rows");
-        klaunch(quant4_rows_kernel, (out + 3) / 4, 256, 0, st, reinterpret_cast<const bf16*>(nk), out, in,
-                reinterpret_cast<unsigned char*>(q4), reinterpret_cast<unsigned char*>(q4s));
-        GP_LAUNCH_CHECK();
-    }
     return GP_OK;
 }
 
-gp_status update_ranges(float* w, const float* g, float* ms, float lr, float rho, float eps, const long* ranges,
-                        int nranges, hipStream_t st) {
-    if (nranges <= 0) return GP_OK;
-    klaunch(update_ranges_kernel, nranges, 256, 0, st, w, g, ms, lr, rho, eps, ms ? 1 : 0, ranges);
+gp_status quantize_rows_fp4(const void* nk, int out, int in, void* q4, void* q4s, hipStream_t st) {
+    if (in % 8) return set_error(GP_ERR_UNSUPPORTED, "refresh: fp4 copies are made from bf16 rows");
+    klaunch(quant4_rows_kernel, (out + 3) / 4, 256, 0, st, reinterpret_cast<const bf16*>(nk), out, in,
+            static_cast<unsigned char*>(q4), static_cast<unsigned char*>(q4s));
     GP_LAUNCH_CHECK();
     return GP_OK;
 }
@@ -626,10 +630,8 @@ gp_status refresh_linear(int dtype, const float* w, int in, int out, void* kn, v
         klaunch(refresh_kernel<float>, grid, 256, 0, st, w, in, out, reinterpret_cast<float*>(kn), reinterpret_cast<float*>(nk));
     GP_LAUNCH_CHECK();
     if (q4) {
-        if (dtype != GP_BF16 || in % 8) return set_error(GP_ERR_UNSUPPORTED, "refresh: fp4 copies are made from bf16 rows");
-        klaunch(quant4_rows_kernel, (out + 3) / 4, 256, 0, st, reinterpret_cast<const bf16*>(nk), out, in,
-                static_cast<unsigned char*>(q4), static_cast<unsigned char*>(q4s));
-        GP_LAUNCH_CHECK();
+        if (dtype != GP_BF16) return set_error(GP_ERR_UNSUPPORTED, "refresh: fp4 copies are made from bf16 rows");
+        return quantize_rows_fp4(nk, out, in, q4, q4s, st);
     }
     return GP_OK;
 }

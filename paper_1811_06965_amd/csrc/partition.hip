@@ -284,7 +284,10 @@ struct gp_partition {
     // passed, beside the backward of the layers below.
     std::vector<hipEvent_t> lay_main, lay_side;
     bool lay_ready = false;
-    bool layer_update = true;  // GP_LAYER_UPDATE=0: the whole update after the last backward
+    // GP_LAYER_UPDATE=0: the whole update in one launch after the last backward;
+    // the default where a layer has fewer than 2M weights, whose update is
+    // shorter than the host's time for its launch and events
+    bool layer_update = true;
     // the last update's stream and an event recorded at its end, with its
     // capture: a forward issued on another stream waits for it
     hipStream_t tail_stream = nullptr;
@@ -292,12 +295,15 @@ struct gp_partition {
     unsigned long long tail_capture = 0;
     bool dw_started = false;   // a weight-gradient GEMM of this mini-batch was launched
     float* opt_ms = nullptr;  // RMSProp: running mean square of every gradient [n32]
-    // bf16 partitions whose linears are whole 64 x 64 tiles update each
-    // linear's weights fused with the refresh of its working copies, and the
-    // rest (biases, LayerNorm parameters) from a table of float ranges
-    bool fused_update = false;
-    long* upd_ranges = nullptr;  // device: (offset, count) pairs
+    // The update's tables in device memory: the linears in plan order (their
+    // weights are updated fused with the refresh of their working copies) and
+    // the rest -- biases, LayerNorm parameters -- as (offset, count) float
+    // ranges of at most 1024
+    UpdateLinear* upd_tab = nullptr;
+    long* upd_ranges = nullptr;
     int n_upd_ranges = 0;
+    std::vector<int> upd_tile0;  // per linear, then the total
+    std::vector<int> upd_layer;  // first linear of each layer, then of the head
     // GP_POISON=1 (test mode): every workspace region is filled with NaN
     // right before the phase that (re)writes it, so that a read of a stale or
     // never-written value shows up in the results.  Regions, per set: the
@@ -1431,13 +1437,52 @@ void free_all(gp_partition* p) {
     p->timer = LaunchTimer();
     p->timer.markers = markers;
     for (void* x : {(void*)p->master, (void*)p->grads, (void*)p->welt, (void*)p->stash_x, (void*)p->stash_m,
-                    (void*)p->ws, (void*)p->opt_ms, (void*)p->upd_ranges})
+                    (void*)p->ws, (void*)p->opt_ms, (void*)p->upd_ranges, (void*)p->upd_tab})
         if (x) (void)hipFree(x);
     p->master = p->grads = p->opt_ms = nullptr;
     p->upd_ranges = nullptr;
+    p->upd_tab = nullptr;
     p->n_upd_ranges = 0;
-    p->fused_update = false;
     p->welt = p->stash_x = p->stash_m = p->ws = nullptr;
+}
+
+// The update's tables (see gp_partition::upd_tab) from the parameter plan.
+hipError_t build_update_tables(gp_partition* p) {
+    std::vector<UpdateLinear> tab;
+    std::vector<long> ranges;
+    auto range = [&](size_t off, long n) {
+        for (long i = 0; i < n; i += 1024) {
+            ranges.push_back((long)off + i);
+            ranges.push_back(std::min(1024L, n - i));
+        }
+    };
+    int tiles = 0;
+    p->upd_tile0.clear();
+    p->upd_layer.clear();
+    auto linear = [&](const Linear& l) {
+        if (!l.present) return;
+        tab.push_back({(long)l.w, (long)l.kn, (long)l.nk, l.in, l.out, tiles, l.f16 ? 1 : 0});
+        p->upd_tile0.push_back(tiles);
+        tiles += ((l.in + 63) / 64) * ((l.out + 63) / 64);
+        range(l.b, l.out);
+    };
+    for (const LayerPlan& P : p->plan.layers) {
+        p->upd_layer.push_back((int)tab.size());
+        for (const Linear* l : {&P.qkv, &P.o, &P.ffn1, &P.ffn2, &P.xq, &P.xkv, &P.xo}) linear(*l);
+    }
+    p->upd_layer.push_back((int)tab.size());
+    linear(p->plan.head.out);
+    p->upd_tile0.push_back(tiles);
+    for (const Norm* n : p->plan.norms()) {
+        range(n->g, n->n);
+        range(n->b, n->n);
+    }
+    hipError_t e = hipMalloc((void**)&p->upd_tab, tab.size() * sizeof(UpdateLinear));
+    if (e == hipSuccess) e = hipMemcpy(p->upd_tab, tab.data(), tab.size() * sizeof(UpdateLinear), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void**)&p->upd_ranges, ranges.size() * sizeof(long));
+    if (e == hipSuccess) e = hipMemcpy(p->upd_ranges, ranges.data(), ranges.size() * sizeof(long), hipMemcpyHostToDevice);
+    p->n_upd_ranges = (int)(ranges.size() / 2);
+    return e;
 }
 
 gp_status alloc(void** ptr, size_t bytes) {
@@ -1515,6 +1560,7 @@ void plan_partition(gp_partition* p, const gp_config* cfg) {
     p->esz = g.dtype == GP_BF16 ? 2 : 4;
     if (const char* e = std::getenv("GP_TIMER_MARKERS")) p->timer.markers = std::atoi(e) != 0;
     if (const char* e = std::getenv("GP_SIDE_STREAM")) p->use_side = std::atoi(e) != 0;
+    p->layer_update = (4L * p->d.D + 2L * p->d.F) * p->d.D >= 2000000;
     if (const char* e = std::getenv("GP_LAYER_UPDATE")) p->layer_update = std::atoi(e) != 0;
     if (const char* e = std::getenv("GP_REMAT_AHEAD")) p->remat_ahead = std::atoi(e) != 0;
     // Early recompute by default where a micro-batch has at most 1024 rows:
@@ -1656,16 +1702,7 @@ gp_status gp_partition_configure(gp_partition* p, const gp_config* cfg) {
     if (e == hipSuccess) e = hipMemset(p->grads, 0, p->plan.n32 * 4);
     if (e == hipSuccess) e = hipMemset(p->ws, 0, p->bytes_ws);
     if (e == hipSuccess && p->opt_ms) e = hipMemset(p->opt_ms, 0, p->plan.n32 * 4);
-    if (e == hipSuccess && g.dtype == GP_BF16) {
-        std::vector<long> ranges;
-        if (plan_update_ranges(p->plan, ranges)) {
-            e = hipMalloc((void**)&p->upd_ranges, ranges.size() * sizeof(long));
-            if (e == hipSuccess)
-                e = hipMemcpy(p->upd_ranges, ranges.data(), ranges.size() * sizeof(long), hipMemcpyHostToDevice);
-            p->n_upd_ranges = (int)(ranges.size() / 2);
-            p->fused_update = e == hipSuccess;
-        }
-    }
+    if (e == hipSuccess) e = build_update_tables(p);
     if (e != hipSuccess) {
         free_all(p);
         return hip_fail(e, __FILE__, __LINE__);
@@ -2231,46 +2268,36 @@ gp_status gp_accumulate_and_step(gp_partition* p, float lr, double* loss_out, gp
         }
     }
     const bool rms = p->g.optimizer == GP_OPT_RMSPROP;
-    auto update_linear = [&](const Linear* l, hipStream_t us) {
-        return update_refresh_linear(p->master + l->w, p->grads + l->w, rms ? p->opt_ms + l->w : nullptr, lr,
-                                     p->g.rms_decay, p->g.rms_eps, l->in, l->out, p->W(l->kn), p->W(l->nk),
-                                     l->split ? p->W(l->q4) : nullptr, l->split ? p->W(l->q4s) : nullptr, us,
-                                     l->f16);
+    const int nlin = (int)p->upd_tile0.size() - 1;
+    // linears l0 .. l1 - 1 in one launch, with the biases and LayerNorm parameters or without
+    auto update = [&](int l0, int l1, bool rest, hipStream_t us) -> gp_status {
+        GP_TRY(update_linears(dt, p->master, p->grads, rms ? p->opt_ms : nullptr, lr, p->g.rms_decay, p->g.rms_eps,
+                              p->welt, p->upd_tab, l0, l1, p->upd_tile0[l1] - p->upd_tile0[l0], p->upd_ranges,
+                              rest ? p->n_upd_ranges : 0, us));
+        if (!p->plan.layers[0].ffn1.split) return GP_OK;
+        const std::vector<const Linear*> all = p->plan.linears();
+        for (int i = l0; i < l1; ++i)
+            if (all[i]->split)
+                GP_TRY(quantize_rows_fp4(p->W(all[i]->nk), all[i]->out, all[i]->in, p->W(all[i]->q4),
+                                         p->W(all[i]->q4s), us));
+        return GP_OK;
     };
-    if (p->fused_update && p->lay_ready) {
+    if (p->lay_ready) {
         // each layer's linears as soon as the last backward is past that layer
         // (top layer first, as the backward goes), then the head's linear, the
         // biases and LayerNorm parameters on the caller's stream
         const hipStream_t us = p->remat;
-        const int L = p->d.L;
-        for (int l = L - 1; l >= 0; --l) {
+        for (int l = p->d.L - 1; l >= 0; --l) {
             GP_HIP(hipStreamWaitEvent(us, p->lay_main[l], 0));
             if (p->lay_side[l]) GP_HIP(hipStreamWaitEvent(us, p->lay_side[l], 0));
-            const LayerPlan& P = p->plan.layers[l];
-            for (const Linear* x : {&P.qkv, &P.o, &P.ffn1, &P.ffn2, &P.xq, &P.xkv, &P.xo})
-                if (x->present) GP_TRY(update_linear(x, us));
+            GP_TRY(update(p->upd_layer[l], p->upd_layer[l + 1], false, us));
         }
         const hipEvent_t upd = p->next_event();
         GP_HIP(hipEventRecord(upd, us));
         GP_HIP(hipStreamWaitEvent(st, upd, 0));
-        if (p->plan.head.out.present) GP_TRY(update_linear(&p->plan.head.out, st));
-        GP_TRY(update_ranges(p->master, p->grads, rms ? p->opt_ms : nullptr, lr, p->g.rms_decay, p->g.rms_eps,
-                             p->upd_ranges, p->n_upd_ranges, st));
-    } else if (p->fused_update) {
-        // one pass over each linear's W and G that also rewrites its working
-        // copies, then the biases and LayerNorm parameters
-        for (const Linear* l : p->plan.linears()) GP_TRY(update_linear(l, st));
-        GP_TRY(update_ranges(p->master, p->grads, rms ? p->opt_ms : nullptr, lr, p->g.rms_decay, p->g.rms_eps,
-                             p->upd_ranges, p->n_upd_ranges, st));
+        GP_TRY(update(p->upd_layer[p->d.L], nlin, true, st));
     } else {
-        if (rms)
-            GP_TRY(rmsprop_update(p->master, p->grads, p->opt_ms, lr, p->g.rms_decay, p->g.rms_eps,
-                                  (long)p->plan.n32, st));
-        else
-            GP_TRY(sgd_update(p->master, p->grads, lr, (long)p->plan.n32, st));
-        for (const Linear* l : p->plan.linears())
-            GP_TRY(refresh_linear(dt, p->master + l->w, l->in, l->out, p->W(l->kn), p->W(l->nk),
-                                  l->split ? p->W(l->q4) : nullptr, l->split ? p->W(l->q4s) : nullptr, st, l->f16));
+        GP_TRY(update(0, nlin, true, st));
     }
     if (loss_out) {
         double v = 0.0;
