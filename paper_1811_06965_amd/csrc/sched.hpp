@@ -226,12 +226,13 @@ inline ParamPlan plan_params(const Dims& d, const Geometry& g) {
     return p;
 }
 
-// The bf16 update pass.  Each linear's W is updated in 64 x 64 tiles in the
-// same pass that rewrites its working copies; every other parameter (the
-// biases, LayerNorm gains and shifts) is updated from a list of (offset,
-// count) float ranges, written to `ranges` as flat pairs.  Returns false (and
-// leaves `ranges` empty) unless every linear is a whole number of tiles and
-// the weights and ranges together cover the n32 master floats exactly once.
+// The parameters outside the linears' weights (biases, LayerNorm gains and
+// shifts) as (offset, count) float ranges, written to `ranges` as flat pairs,
+// with a check of the plan: returns false (and leaves `ranges` empty) unless
+// every linear is a whole number of 64 x 64 tiles and the weights and ranges
+// together cover the n32 master floats exactly once.  The update itself takes
+// any plan (its tables are built with the partition); the host tests use this
+// to show that a plan leaves no gap and no overlap.
 inline bool plan_update_ranges(const ParamPlan& p, std::vector<long>& ranges) {
     ranges.clear();
     std::vector<std::pair<size_t, size_t>> cover;  // (offset, count) of every block
