@@ -175,10 +175,10 @@ struct UpdateLinear {
 // The SGD (ms == nullptr) or RMSProp step of linears l0 .. l1 - 1 (`tiles` tiles)
 // fused with the refresh of their working copies as refresh_linear makes them
 // (fp4 copies excepted), and of nranges float ranges (offset, count pairs in
-// device memory): one launch.
+// device memory; apart: their roundings, see update_one): one launch.
 gp_status update_linears(int dtype, float* master, const float* grads, float* ms, float lr, float rho, float eps,
                          void* welt, const UpdateLinear* table, int l0, int l1, int tiles, const long* ranges,
-                         int nranges, hipStream_t st);
+                         int nranges, int apart, hipStream_t st);
 // An empty launch labelled by its grid (role x (edge + 1) workgroups of one
 // wave): edge 0 before, 1 after a timed launch, so that per-dispatch profiler
 // records can be attributed to launch roles.

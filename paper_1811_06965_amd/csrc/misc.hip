@@ -306,13 +306,19 @@ __global__ void __launch_bounds__(256) refresh_bf16_tiles(const float* __restric
 }
 
 // W <- W - lr G (SGD), or the RMSProp step (rms: ms <- rho ms + (1 - rho) G^2;
-// W <- W - lr G / sqrt(ms + eps)), of one parameter.
-__device__ __forceinline__ float update_one(float w, float g, float& m, float lr, float rho, float eps, int rms) {
+// W <- W - lr G / sqrt(ms + eps)), of one parameter.  Which product goes unrounded
+// into its sum is written out, since what the compiler fuses by itself changes with
+// the code around: W and ms take fma(-lr, G, W) and fma(rho, ms, (1 - rho) G^2);
+// `apart` (see update_kernel): W - (lr G) and fma(1 - rho, G^2, rho ms).
+__device__ __forceinline__ float update_one(float w, float g, float& m, float lr, float rho, float eps, int rms,
+                                            int apart) {
+#pragma clang fp contract(off)
     if (rms) {
-        m = rho * m + (1.f - rho) * (g * g);
+        const float gg = g * g, k = 1.f - rho;
+        m = apart ? __builtin_fmaf(k, gg, rho * m) : __builtin_fmaf(rho, m, k * gg);
         w -= lr * g / sqrtf(m + eps);
     } else {
-        w -= lr * g;
+        w = apart ? w - lr * g : __builtin_fmaf(-lr, g, w);
     }
     return w;
 }
@@ -322,7 +328,9 @@ __device__ __forceinline__ float update_one(float w, float g, float& m, float lr
 // linears end to end, from linear l0's first) reads W and G once and writes W,
 // the copy kn and, through an LDS tile, the transposed copy nk; 16-byte accesses
 // where in and out are multiples of 64.  Workgroups from `tiles` on update the
-// parameters outside the weights: workgroup tiles + r the float range r.
+// parameters outside the weights: workgroup tiles + r the float range r, with the
+// roundings of `apart` where every linear is whole tiles in bf16 (a kernel of their
+// own updated them there, and the results keep its bits).
 // Bound by HBM for large layers (16 bytes per weight with SGD, 12 with fp32
 // copies); for small ones by the launches, which one per linear, plus one for
 // the rest, cost 5 us of host time each: the smallest fp32 step 1085 -> 959 us,
@@ -331,14 +339,14 @@ template <typename T>
 __global__ void __launch_bounds__(256) update_kernel(float* __restrict__ master, const float* __restrict__ grads,
                                                      float* __restrict__ ms, float lr, float rho, float eps, int rms,
                                                      T* __restrict__ welt, const UpdateLinear* __restrict__ tab, int l0,
-                                                     int l1, int tiles, const long* __restrict__ ranges) {
+                                                     int l1, int tiles, const long* __restrict__ ranges, int apart) {
     __shared__ float tile[64][65];
     const int t = threadIdx.x;
     if ((int)blockIdx.x >= tiles) {
         const long r = blockIdx.x - tiles, off = ranges[2 * r], n = ranges[2 * r + 1];
         for (long i = off + t; i < off + n; i += 256) {
             float m = rms ? ms[i] : 0.f;
-            master[i] = update_one(master[i], grads[i], m, lr, rho, eps, rms);
+            master[i] = update_one(master[i], grads[i], m, lr, rho, eps, rms, apart);
             if (rms) ms[i] = m;
         }
         return;
@@ -371,7 +379,7 @@ __global__ void __launch_bounds__(256) update_kernel(float* __restrict__ master,
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float me = m[e];
-                v[e] = update_one(v[e], gv[e], me, lr, rho, eps, rms);
+                v[e] = update_one(v[e], gv[e], me, lr, rho, eps, rms, 0);
                 m[e] = me;
             }
             if (rms) *reinterpret_cast<f32x4*>(mm + o) = m;
@@ -399,7 +407,7 @@ __global__ void __launch_bounds__(256) update_kernel(float* __restrict__ master,
         if (row < u.in && col < u.out) {
             const long o = (long)row * u.out + col;
             float m = rms ? mm[o] : 0.f;
-            const float v = update_one(w[o], g[o], m, lr, rho, eps, rms);
+            const float v = update_one(w[o], g[o], m, lr, rho, eps, rms, 0);
             if (rms) mm[o] = m;
             w[o] = v;
             tile[r][tx] = v;
@@ -593,14 +601,14 @@ gp_status mfma_peak(hipStream_t st, double* tflops) {
 
 gp_status update_linears(int dtype, float* master, const float* grads, float* ms, float lr, float rho, float eps,
                          void* welt, const UpdateLinear* table, int l0, int l1, int tiles, const long* ranges,
-                         int nranges, hipStream_t st) {
+                         int nranges, int apart, hipStream_t st) {
     if (tiles + nranges <= 0) return GP_OK;
     if (dtype == GP_BF16)
         klaunch(update_kernel<bf16>, tiles + nranges, 256, 0, st, master, grads, ms, lr, rho, eps, ms ? 1 : 0,
-                static_cast<bf16*>(welt), table, l0, l1, tiles, ranges);
+                static_cast<bf16*>(welt), table, l0, l1, tiles, ranges, apart);
     else
         klaunch(update_kernel<float>, tiles + nranges, 256, 0, st, master, grads, ms, lr, rho, eps, ms ? 1 : 0,
-                static_cast<float*>(welt), table, l0, l1, tiles, ranges);
+                static_cast<float*>(welt), table, l0, l1, tiles, ranges, apart);
     GP_LAUNCH_CHECK();
     return GP_OK;
 }

@@ -302,6 +302,7 @@ struct gp_partition {
     UpdateLinear* upd_tab = nullptr;
     long* upd_ranges = nullptr;
     int n_upd_ranges = 0;
+    int upd_apart = 0;           // bf16 with every linear in whole tiles: the ranges' roundings (update_one)
     std::vector<int> upd_tile0;  // per linear, then the total
     std::vector<int> upd_layer;  // first linear of each layer, then of the head
     // GP_POISON=1 (test mode): every workspace region is filled with NaN
@@ -1457,12 +1458,14 @@ hipError_t build_update_tables(gp_partition* p) {
         }
     };
     int tiles = 0;
+    p->upd_apart = p->g.dtype == GP_BF16;
     p->upd_tile0.clear();
     p->upd_layer.clear();
     auto linear = [&](const Linear& l) {
         if (!l.present) return;
         tab.push_back({(long)l.w, (long)l.kn, (long)l.nk, l.in, l.out, tiles, l.f16 ? 1 : 0});
         p->upd_tile0.push_back(tiles);
+        if (l.in % 64 || l.out % 64) p->upd_apart = 0;
         tiles += ((l.in + 63) / 64) * ((l.out + 63) / 64);
         range(l.b, l.out);
     };
@@ -2273,7 +2276,7 @@ gp_status gp_accumulate_and_step(gp_partition* p, float lr, double* loss_out, gp
     auto update = [&](int l0, int l1, bool rest, hipStream_t us) -> gp_status {
         GP_TRY(update_linears(dt, p->master, p->grads, rms ? p->opt_ms : nullptr, lr, p->g.rms_decay, p->g.rms_eps,
                               p->welt, p->upd_tab, l0, l1, p->upd_tile0[l1] - p->upd_tile0[l0], p->upd_ranges,
-                              rest ? p->n_upd_ranges : 0, us));
+                              rest ? p->n_upd_ranges : 0, p->upd_apart, us));
         if (!p->plan.layers[0].ffn1.split) return GP_OK;
         const std::vector<const Linear*> all = p->plan.linears();
         for (int i = l0; i < l1; ++i)

@@ -1,0 +1,66 @@
+"""The bits of a step's outputs.  A result of the library does not depend on the
+kernel form that a size takes: where a wider or grouped form took a simpler one's
+place, it adds in the simpler one's order.  tests/golden/step_bits.json holds
+digests of each output as the simpler forms gave them (a wave per row in LayerNorm
+and cross-entropy, one launch and its split-K reduce per weight gradient, the
+register-staged GEMM for reductions that are no multiple of 64)."""
+import hashlib
+import json
+import os
+
+import numpy as np
+import pytest
+
+import synth
+from parity import to_np
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "step_bits.json")
+
+
+def _cfg(name, **kw):
+    return synth.PartitionConfig(name, **dict(dict(layers=2, d_model=64, d_ff=128, heads=1, seq=32, batch=3, micro=3,
+                                                   dtype="bf16"), **kw))
+
+
+CASES = [
+    # the update: weights in whole tiles, biases and gains; SGD and RMSProp in both types
+    _cfg("sgd", d_model=128, heads=2, d_ff=256),
+    _cfg("rmsprop", d_model=128, heads=2, d_ff=256, loss="mse", optimizer="rmsprop"),
+    _cfg("sgd_f32", d_model=72, heads=6, d_ff=200, seq=20, dtype="f32"),
+    _cfg("rmsprop_f32", d_model=72, heads=6, d_ff=200, seq=20, dtype="f32", loss="mse", optimizer="rmsprop"),
+]
+
+
+def digests(cfg):
+    from paper_1811_06965_amd.runtime import Partition
+    case = synth.make_case(cfg, 9, perturb=True)
+    with Partition(cfg) as part:
+        part.load_params(case["layers"], case["head"])
+        inp = part.device_inputs(case)
+        for _ in range(2):  # the second step accumulates afresh, on updated weights
+            out = part.step(inp["x"], inp["mem"], inp["dy"], lr=1e-2 if cfg.optimizer == "sgd" else 1e-3)
+        gl, gh = part.grads()
+        pl, ph = part.params()
+    res = {k: to_np(out[k]) for k in ("y", "dx", "dmem") if out[k] is not None}
+    if out["loss"] is not None:
+        res["loss"] = np.float32([out["loss"]])
+    for l, g in enumerate(gl + [gh]):
+        res.update({f"{l}.{k}": v for k, v in g.items()})
+    for l, w in enumerate(pl + [ph]):
+        res.update({f"{l}.{k}.updated": v for k, v in w.items()})
+    # + 0: a zero has one sign
+    return {k: hashlib.sha256(np.ascontiguousarray(v + v.dtype.type(0)).tobytes()).hexdigest()[:12]
+            for k, v in res.items()}
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_outputs_keep_their_bits(cfg):
+    with open(GOLDEN) as f:
+        want = json.load(f)[cfg.name]
+    got = digests(cfg)
+    assert sorted(got) == sorted(want)
+    assert [k for k in want if got[k] != want[k]] == []
