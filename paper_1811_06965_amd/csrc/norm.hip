@@ -389,37 +389,45 @@ __global__ void __launch_bounds__(256) ln_bwd_v4(const float* __restrict__ dn, c
     }
 }
 
-// The LayerNorm backward for wide rows: the block's 256 threads share a row
-// (thread t owns float4 chunks t + 256 c), two rows at a time, with the row
-// sums exchanged through 128 bytes of LDS per pair; a thread keeps its
-// features' parameter sums for the block's rows (the same 4 rpw rows as
-// ln_bwd_v4, summed in row order).  ln_bwd_v4's wave per row takes 469 VGPRs
-// and 64 KB of LDS at D = 2048, so that beside a weight-gradient or recompute
-// GEMM it waits for a whole CU to drain: 109 us per launch in a step at 1024
-// rows of 2048, 58 in this form (floor 8), and the step of one d_model 2048
-// layer 30.0 -> 29.1 ms.  At D = 1024 (226 VGPRs, 32 KB) the 2-layer decoder
-// 19.7 -> 19.3 ms and the 16-layer encoder 65.1 -> 64.2; narrower rows keep the
-// wave per row.
-template <typename T, int CW>
+// The LayerNorm backward for wide rows (D = 256 C4, C4 >= 4): the block's 256
+// threads share a row, two rows at a time.  ln_bwd_v4's wave per row takes 469
+// VGPRs and 64 KB of LDS at D = 2048, so that beside a weight-gradient or
+// recompute GEMM it waits for a whole CU to drain: 107 us per launch in a step at
+// 1024 rows of 2048, 60 in this form (floor 8); at D = 1024 (226 VGPRs, 32 KB) 38.5
+// and 28 at 2048 rows, 17.5 and 16 at 1024.  Narrower rows keep the wave per row.
+//
+// Every value is the wave-per-row form's, bit for bit: wave w owns the 64-lane
+// chunks w, w + 4, .. of the row; the chunks' sums meet in LDS, where one wave per
+// row and sum adds a lane's C4 of them in chunk order before the sum over the
+// lanes; the parameter sums of each run of rpw rows are added up apart, then run
+// after run.  The fused
+// multiply-adds are written out (the compiler fuses nothing here by itself): they
+// are those that ln_bwd_v4's expressions compile to, where the first chunk's
+// product with gamma goes unrounded into the subtraction of the mean.
+template <typename T, int C4>
 __global__ void __launch_bounds__(256) ln_bwd_wide(const float* __restrict__ dn, const float* __restrict__ x,
                                                    const float* __restrict__ stats, const float* __restrict__ gamma,
                                                    long rows, int D, int rpw, const float* __restrict__ dres,
                                                    float* __restrict__ dx32, T* __restrict__ dxe,
                                                    float* __restrict__ partial, int accumulate, int dn_splits,
                                                    long dn_plane) {
-    __shared__ float red[2][2][4][2];  // [parity of the pair][row][wave][sum]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n4 = D / 4;
+#pragma clang fp contract(off)
+    constexpr int CW = (C4 + 3) / 4;  // chunks a wave owns (the last one: waves below C4 % 4, if that is not 0)
+    __shared__ float red[2][2][C4][64];  // [row of the pair][sum of g, of g xh][chunk][lane]
+    __shared__ float mean[2][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const f32x4* g4 = reinterpret_cast<const f32x4*>(gamma);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 pg[CW], pb[CW], gm[CW];
+    f32x4 pg[CW], pb[CW], tg[CW], tb[CW], gm[CW];  // parameter sums of this run of rows, of the runs before
 #pragma unroll
     for (int c = 0; c < CW; ++c) {
-        pg[c] = pb[c] = zero;
-        gm[c] = tid + 256 * c < n4 ? g4[tid + 256 * c] : zero;
+        pg[c] = pb[c] = tg[c] = tb[c] = zero;
+        gm[c] = wave + 4 * c < C4 ? g4[tid + 256 * c] : zero;
     }
+    auto fma4 = [](f32x4 a, f32x4 b, f32x4 c) { return __builtin_elementwise_fma(a, b, c); };
     const long row0 = (long)blockIdx.x * LN_WAVES * rpw, end = min(rows, row0 + (long)LN_WAVES * rpw);
-    int par = 0;
-    for (long row = row0; row < end; row += 2, par ^= 1) {
+    int in_run = 0;
+    for (long row = row0; row < end; row += 2) {
         f32x4 dv[2][CW], xh[2][CW], rv[2][CW];
         float mu[2], rstd[2];
 #pragma unroll
@@ -435,50 +443,59 @@ __global__ void __launch_bounds__(256) ln_bwd_wide(const float* __restrict__ dn,
             for (int c = 0; c < CW; ++c) {
                 const int i = tid + 256 * c;
                 dv[r][c] = xh[r][c] = rv[r][c] = zero;
-                if (i >= n4 || !live) continue;
+                if (wave + 4 * c >= C4 || !live) continue;
                 dv[r][c] = dn4[i];
                 for (int k = 1; k < dn_splits; ++k) dv[r][c] += dn4[i + k * (dn_plane / 4)];
                 xh[r][c] = x4[i];
                 if (dres) rv[r][c] = r4[i];
             }
         }
-        float s[2][2];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            s[r][0] = s[r][1] = 0.f;
-#pragma unroll
-            for (int c = 0; c < CW; ++c) {
-                if (tid + 256 * c >= n4) continue;
-                xh[r][c] = (xh[r][c] - mu[r]) * rstd[r];
-                const f32x4 g = dv[r][c] * gm[c];
-                if (row + r < end) {
-                    pg[c] += dv[r][c] * xh[r][c];
-                    pb[c] += dv[r][c];
-                }
-                s[r][0] += hsum(g);
-                s[r][1] += hsum(g * xh[r][c]);
-            }
-            s[r][0] = wave_sum(s[r][0]);
-            s[r][1] = wave_sum(s[r][1]);
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                red[par][r][wave][0] = s[r][0];
-                red[par][r][wave][1] = s[r][1];
-            }
-        }
-        __syncthreads();  // one per pair: the other parity's sums were read before this one's barrier
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             if (row + r >= end) break;
-            const float sg = ((red[par][r][0][0] + red[par][r][1][0]) + (red[par][r][2][0] + red[par][r][3][0])) / D;
-            const float sgx = ((red[par][r][0][1] + red[par][r][1][1]) + (red[par][r][2][1] + red[par][r][3][1])) / D;
+            const bool run_ends = ++in_run == rpw;
+            if (run_ends) in_run = 0;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                if (wave + 4 * c >= C4) continue;
+                xh[r][c] = (xh[r][c] - mu[r]) * rstd[r];
+                const f32x4 d = dv[r][c], h = xh[r][c], w = gm[c], g = d * w;
+                pg[c] = fma4(d, h, pg[c]);
+                pb[c] += d;
+                if (run_ends) {
+                    tg[c] += pg[c];
+                    tb[c] += pb[c];
+                    pg[c] = pb[c] = zero;
+                }
+                red[r][0][wave + 4 * c][lane] = __builtin_fmaf(d[0], w[0], g[1]) + __builtin_fmaf(d[2], w[2], g[3]);
+                red[r][1][wave + 4 * c][lane] =
+                    __builtin_fmaf(g[0], h[0], g[1] * h[1]) + __builtin_fmaf(g[2], h[2], g[3] * h[3]);
+                if (wave + 4 * c != 0) dv[r][c] = g;
+            }
+        }
+        __syncthreads();
+        {
+            const int r = wave >> 1, k = wave & 1;
+            float t = 0.f;
+            if (row + r < end) {
+#pragma unroll
+                for (int c = 0; c < C4; ++c) t += red[r][k][c][lane];
+                t = wave_sum(t) / D;
+                if (lane == 0) mean[r][k] = t;
+            }
+        }
+        __syncthreads();  // also: red is read before the next pair's sums go there
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (row + r >= end) break;
+            const float sg = mean[r][0], sgx = mean[r][1];
 #pragma unroll
             for (int c = 0; c < CW; ++c) {
                 const int i = tid + 256 * c;
-                if (i >= n4) continue;
-                const f32x4 v = rstd[r] * (dv[r][c] * gm[c] - sg - xh[r][c] * sgx) + rv[r][c];
+                if (wave + 4 * c >= C4) continue;
+                f32x4 v = wave + 4 * c == 0 ? fma4(dv[r][c], gm[c], zero - sg) : dv[r][c] - sg;
+                v = fma4(zero - sgx, xh[r][c], v);
+                v = fma4(zero + rstd[r], v, rv[r][c]);
                 if (dx32) reinterpret_cast<f32x4*>(dx32 + (row + r) * D)[i] = v;
                 if (dxe) Out4<T>::store(dxe + (row + r) * D + 4 * i, v);
             }
@@ -488,13 +505,17 @@ __global__ void __launch_bounds__(256) ln_bwd_wide(const float* __restrict__ dn,
 #pragma unroll
     for (int c = 0; c < CW; ++c) {
         const int i = tid + 256 * c;
-        if (i >= n4) continue;
-        if (accumulate) {
-            pg[c] += pp[i];
-            pb[c] += pp[n4 + i];
+        if (wave + 4 * c >= C4) continue;
+        if (in_run) {  // a run cut off at the last row
+            tg[c] += pg[c];
+            tb[c] += pb[c];
         }
-        pp[i] = pg[c];
-        pp[n4 + i] = pb[c];
+        if (accumulate) {
+            tg[c] += pp[i];
+            tb[c] += pp[D / 4 + i];
+        }
+        pp[i] = tg[c];
+        pp[D / 4 + i] = tb[c];
     }
 }
 
@@ -540,20 +561,20 @@ gp_status ln_bwd_t(const float* dn, const float* x, const float* stats, const fl
     if (D % 256 == 0 && D <= 2048) {
 #define GP_LNV(CC) klaunch(ln_bwd_v4<T, CC>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e, partial, \
                            accumulate, dn_splits, dn_plane)
+#define GP_LNW(CC) klaunch(ln_bwd_wide<T, CC>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e, \
+                           partial, accumulate, dn_splits, dn_plane)
         switch (D / 256) {
         case 1: GP_LNV(1); break;
         case 2: GP_LNV(2); break;
         case 3: GP_LNV(3); break;
-        case 4:
-            klaunch(ln_bwd_wide<T, 1>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e,
-                    partial, accumulate, dn_splits, dn_plane);
-            break;
-        default:
-            klaunch(ln_bwd_wide<T, 2>, grid, 256, 0, st, dn, x, stats, gamma, rows, D, rpw, dres, dx32, e,
-                    partial, accumulate, dn_splits, dn_plane);
-            break;
+        case 4: GP_LNW(4); break;
+        case 5: GP_LNW(5); break;
+        case 6: GP_LNW(6); break;
+        case 7: GP_LNW(7); break;
+        default: GP_LNW(8); break;
         }
 #undef GP_LNV
+#undef GP_LNW
         GP_LAUNCH_CHECK();
         return GP_OK;
     }

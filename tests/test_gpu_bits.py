@@ -32,6 +32,18 @@ CASES = [
     _cfg("rmsprop", d_model=128, heads=2, d_ff=256, loss="mse", optimizer="rmsprop"),
     _cfg("sgd_f32", d_model=72, heads=6, d_ff=200, seq=20, dtype="f32"),
     _cfg("rmsprop_f32", d_model=72, heads=6, d_ff=200, seq=20, dtype="f32", loss="mse", optimizer="rmsprop"),
+    # LayerNorm backward of wide rows, a block per row: one and two chunks per
+    # thread, the second one for some of the waves only; odd row counts
+    _cfg("ln1024", d_model=1024, heads=16, batch=6),
+    _cfg("ln2048", layers=1, d_model=2048, heads=32, batch=6),
+    _cfg("ln1280_f32", layers=1, d_model=1280, heads=20, seq=12, batch=2, micro=2, dtype="f32", loss="mse"),
+    _cfg("ln1536", layers=1, d_model=1536, heads=24, batch=2, micro=2),
+    _cfg("ln1792_f32", layers=1, d_model=1792, heads=28, seq=20, batch=1, micro=1, dtype="f32", loss="mse"),
+    # several rows per run of the parameter sums, the last run and block cut off
+    _cfg("ln1024_rows", layers=1, d_model=1024, heads=16, d_ff=64, seq=513, batch=4, micro=1, dtype="f32", loss="mse"),
+    _cfg("ln2048_rows", layers=1, d_model=2048, heads=32, d_ff=64, seq=1023, batch=4, micro=1, dtype="f32", loss="mse"),
+    # its input still in split-K partial sums
+    _cfg("ln1024_partials", d_model=1024, heads=16, d_ff=8192, seq=128, batch=2, micro=2),
 ]
 
 
