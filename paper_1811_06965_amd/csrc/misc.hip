@@ -161,43 +161,56 @@ __global__ void __launch_bounds__(256) xent_kernel(T* __restrict__ z, int V, con
     if (tid == 0) partial[row] = ((double)lse - (double)u * sz - (1.0 - ls) * zl) / norm;
 }
 
-// The same for bf16 logits with the row held in registers: NC chunks of 8
-// logits per thread (V % 8 == 0, V <= 2048 NC), read once and written once
-// with 16-byte accesses (the kernel above reads the row four times in 2-byte
-// accesses).  Bound by HBM: at 1024 rows of 32000, 131 MB, 26 us at the copy
-// rate; 151 us before, 54 now (both inside a step, beside other streams).
-template <int NC>
+// The same for bf16 logits (V % 8 == 0, V <= 2048 NC) with the row in LDS: read
+// once and written once with 16-byte accesses, where the kernel above reads it four
+// times in 2-byte accesses.  A thread works on the same logits in the same order as
+// there (v = tid + 256 k), its exponentials stay in registers, and the fused
+// multiply-adds are those that kernel compiles to, so the results are the same bit
+// for bit.  Bound by HBM and the exponentials' vector instructions: at 1024 rows of
+// 32000, 131 MB, 26 us at the copy rate and about as much for the latter; 154 us
+// before, 63 now (both inside a step, beside other streams).
+template <int NC, bool CLIP>
 __global__ void __launch_bounds__(256) xent_rows_kernel(bf16* __restrict__ z, int V, const int* __restrict__ labels,
                                                         float ls, float clip, double norm,
                                                         double* __restrict__ partial, int* __restrict__ bad_label) {
+    constexpr int K = 8 * NC;
+    __shared__ __attribute__((aligned(16))) bf16 zs[NC * 2048];
     __shared__ float red[3][4];
     const long row = blockIdx.x;
-    bf16* zr = z + row * (long)V;
-    bf16x8* z8 = reinterpret_cast<bf16x8*>(zr);
+    bf16x8* z8 = reinterpret_cast<bf16x8*>(z + row * (long)V);
+    bf16x8* s8 = reinterpret_cast<bf16x8*>(zs);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, n8 = V / 8;
-    const float lim = clip > 0.f ? clip : INFINITY;
+    const int kf = V / 256, rest = kf * 256 + tid;  // logits of every thread, and this thread's one beyond them
+    const float lim = CLIP ? clip : INFINITY;
+    auto logit = [&](int v) {  // no clip: a NaN counts as -inf, as it does between two limits
+        const float x = fmaxf((float)zs[v], -lim);
+        return CLIP ? fminf(x, lim) : x;
+    };
     const int raw = labels[row];
     const bool ok = raw >= 0 && raw < V;
     const int lab = ok ? raw : 0;
     if (!ok && tid == 0) bad_label[0] = 1;
-    const float zl = fminf(fmaxf((float)zr[lab], -lim), lim);
     bf16x8 v[NC];
-    float m = -INFINITY, sz = 0.f;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int i = tid + 256 * c;
-        if (i >= n8) break;
-        v[c] = z8[i];
+    for (int c = 0; c < NC; ++c)
+        if (tid + 256 * c < n8) v[c] = z8[tid + 256 * c];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (tid + 256 * c < n8) s8[tid + 256 * c] = v[c];
+    __syncthreads();
+    const float zl = logit(lab), raw_lab = (float)zs[lab];
+    float ex[K], xr = -INFINITY, m = -INFINITY, sz = 0.f, se = 0.f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (256 * k + 255 >= V) break;
+        ex[k] = logit(tid + 256 * k);
+        m = fmaxf(m, ex[k]);
+        sz += ex[k];
     }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        if (tid + 256 * c >= n8) break;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = fminf(fmaxf((float)v[c][e], -lim), lim);
-            m = fmaxf(m, x);
-            sz += x;
-        }
+    if (rest < V) {
+        xr = logit(rest);
+        m = fmaxf(m, xr);
+        sz += xr;
     }
     m = wave_max(m);
     sz = wave_sum(sz);
@@ -205,37 +218,43 @@ __global__ void __launch_bounds__(256) xent_rows_kernel(bf16* __restrict__ z, in
         red[0][w] = m;
         red[1][w] = sz;
     }
-    __syncthreads();  // also: every thread has read zl and its chunks
+    __syncthreads();  // also: every thread has read the label's logit
     m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-    sz = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-    float ex[NC][8], se = 0.f;
+    sz = red[1][0] + red[1][1] + red[1][2] + red[1][3];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        if (tid + 256 * c >= n8) break;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            ex[c][e] = expf(fminf(fmaxf((float)v[c][e], -lim), lim) - m);
-            se += ex[c][e];
-        }
+    for (int k = 0; k < K; ++k) {
+        if (256 * k + 255 >= V) break;
+        ex[k] = expf(ex[k] - m);
+        se += ex[k];
+    }
+    if (rest < V) {
+        xr = expf(xr - m);
+        se += xr;
     }
     se = wave_sum(se);
     if (lane == 0) red[2][w] = se;
     __syncthreads();
-    se = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+    se = red[2][0] + red[2][1] + red[2][2] + red[2][3];
     const float inv = 1.f / se, u = ls / V, gn = (float)(1.0 / norm);
+    auto grad = [&](float logit, float e, float q) {
+        return (bf16)(fabsf(logit) <= lim ? __builtin_fmaf(e, inv, -q) * gn : 0.f);
+    };
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int i = tid + 256 * c;
-        if (i >= n8) break;
-        bf16x8 o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float p = ex[c][e] * inv, q = u + (8 * i + e == lab ? 1.f - ls : 0.f);
-            o[e] = (bf16)(fabsf((float)v[c][e]) <= lim ? (p - q) * gn : 0.f);
-        }
-        z8[i] = o;
+    for (int k = 0; k < K; ++k) {
+        if (256 * k + 255 >= V) break;
+        const int i = tid + 256 * k;
+        zs[i] = grad((float)zs[i], ex[k], u);
     }
-    if (tid == 0) partial[row] = ((double)(m + logf(se)) - (double)u * sz - (1.0 - ls) * zl) / norm;
+    if (rest < V) zs[rest] = grad((float)zs[rest], xr, u);
+    if (tid == (lab & 255)) zs[lab] = grad(raw_lab, expf(zl - m), u + (1.f - ls));
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (tid + 256 * c < n8) z8[tid + 256 * c] = s8[tid + 256 * c];
+    if (tid == 0) {
+        const double lse = m + logf(se);
+        partial[row] = __builtin_fma(-(1.0 - ls), (double)zl, __builtin_fma(-(double)u, (double)sz, lse)) / norm;
+    }
 }
 
 // kn = W, nk = W^T through a 64 x 64 LDS tile (both writes coalesced).
@@ -550,12 +569,25 @@ gp_status xent_ls(int dtype, void* z, long rows, int V, const int* labels, float
     if (dtype == GP_BF16 && V % 8 == 0 && V <= 16 * 2048) {
         bf16* zb = reinterpret_cast<bf16*>(z);
         const int nc = (V + 2047) / 2048;
-#define GP_XENT(NC) klaunch(xent_rows_kernel<NC>, (unsigned)rows, 256, 0, st, zb, V, labels, ls, clip, norm, partial, bad_label)
-        if (nc <= 1) GP_XENT(1);
-        else if (nc <= 2) GP_XENT(2);
-        else if (nc <= 4) GP_XENT(4);
-        else if (nc <= 8) GP_XENT(8);
-        else GP_XENT(16);
+#define GP_XENT(NC)                                                                                                  \
+    do {                                                                                                             \
+        if (clip > 0.f)                                                                                              \
+            klaunch(xent_rows_kernel<NC, true>, (unsigned)rows, 256, 0, st, zb, V, labels, ls, clip, norm, partial,  \
+                    bad_label);                                                                                      \
+        else                                                                                                         \
+            klaunch(xent_rows_kernel<NC, false>, (unsigned)rows, 256, 0, st, zb, V, labels, ls, clip, norm, partial, \
+                    bad_label);                                                                                      \
+    } while (0)
+        if (nc <= 1)
+            GP_XENT(1);
+        else if (nc <= 2)
+            GP_XENT(2);
+        else if (nc <= 4)
+            GP_XENT(4);
+        else if (nc <= 8)
+            GP_XENT(8);
+        else
+            GP_XENT(16);
 #undef GP_XENT
     } else if (dtype == GP_BF16)
         klaunch(xent_kernel<bf16>, (unsigned)rows, 256, 0, st, reinterpret_cast<bf16*>(z), V, labels, ls, clip, norm,

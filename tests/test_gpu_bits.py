@@ -44,6 +44,11 @@ CASES = [
     _cfg("ln2048_rows", layers=1, d_model=2048, heads=32, d_ff=64, seq=1023, batch=4, micro=1, dtype="f32", loss="mse"),
     # its input still in split-K partial sums
     _cfg("ln1024_partials", d_model=1024, heads=16, d_ff=8192, seq=128, batch=2, micro=2),
+] + [
+    # cross-entropy rows: register chunks of one to sixteen times 2048 logits and their edges
+    _cfg("xent%d" % v, layers=1, batch=6, loss="xent_ls", vocab=v, label_smoothing=0.1, logit_clip=c)
+    for v, c in ((64, 0.0), (264, 0.3), (2048, 0.3), (2112, 0.0), (4160, 0.3), (8256, 0.0), (16448, 0.0), (32000, 0.0),
+                 (32768, 0.3))
 ]
 
 
