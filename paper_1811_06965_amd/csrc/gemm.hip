@@ -635,13 +635,18 @@ __device__ __forceinline__ bf16x8 tr_frag(const char* p, int second) {
 // (one k-group, no fp4 stage).  The register-staged kernel that such reductions
 // fell back to took 8.0 us per 288 x 320 x 1000 GEMM, this 6.7 (with the rest
 // of the layer, in a step).
+// SEG: the k-tiles are added up in segments of args.seg tiles, each from zero,
+// and the segments in their order: bit for bit a split-K launch and its reduce,
+// without the partial tiles in memory (32 registers; unsplit, one k-group).
 // One output tile (tm, tn); under split-K the k-tiles of split `split` of `nsplits`.
-template <int BM, int BN, int WM, int WN, int NSTAGE, int EPI, int SM, bool KM, bool MX, int KG, bool F16, bool RAG>
+template <int BM, int BN, int WM, int WN, int NSTAGE, int EPI, int SM, bool KM, bool MX, int KG, bool F16, bool RAG,
+          bool SEG = false>
 __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int tn, int split, int nsplits) {
     static_assert(!RAG || (!MX && KG == 1), "ragged K: one k-group, no fp4 stage");
     static_assert(!F16 || (KM && !MX && KG == 1), "fp16 operands: k-contiguous, no fp4 stage, one k-group");
     // SM: 0 no split-K; 1 split-K, partial tiles only (summed by splitk_reduce)
     constexpr bool SPLIT = SM != 0;
+    static_assert(!SEG || (!SPLIT && KG == 1), "segments: unsplit, one k-group");
     constexpr int BK = 64, KS = 4, NW = WM * WN;  // NW: waves per k-group
     static_assert(KG == 1 || (KG == 2 && KM && !MX && !SPLIT), "k-groups: k-contiguous, unsplit, bf16 only");
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -855,6 +860,32 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
 #pragma unroll
     for (int j = 0; j < TN; ++j) cs[j] = 0.f;
 
+    // SEG: the segments before this one
+    f32x16 tot[SEG ? TM : 1][SEG ? TN : 1];
+    float tcs[SEG ? TN : 1];
+    bool folded = false;
+    int fold_at = SEG ? args.seg : 0;
+    auto fold = [&]() {
+        if constexpr (SEG) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        tot[i][j][r] = folded ? tot[i][j][r] + acc[i][j][r] : acc[i][j][r];
+                        acc[i][j][r] = 0.f;
+                    }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const float c = cs[j] + __shfl_xor(cs[j], 32);
+                tcs[j] = folded ? tcs[j] + c : c;
+                cs[j] = 0.f;
+            }
+            folded = true;
+        }
+    };
+
     if (nkt > 0) {
         // prologue: fill every stage; wait for tile 0 (tiles 1 .. NSTAGE-1 may be in flight)
 #pragma unroll
@@ -872,6 +903,12 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
             for (int st = 0; st < NSTAGE; ++st) {
                 const int i = i0 + st;
                 if (i >= nkt) break;
+                if constexpr (SEG) {
+                    if (i == fold_at) {
+                        fold();
+                        fold_at += args.seg;
+                    }
+                }
                 const char* stg = smem + st * STAGE;
                 const char* nxt = smem + ((st + 1) % NSTAGE) * STAGE;
 #pragma unroll
@@ -973,11 +1010,25 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * TN + j) * 16 + r) * 64];
     }
+    if constexpr (SEG) {
+        if (folded) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = tot[i][j][r] + acc[i][j][r];
+        }
+    }
     const int row0 = m0 + wm * (BM / WM), col0 = n0 + wn * (BN / WN) + (lane & 31);
     if constexpr (COLSUM) {
         // lanes l and l + 32 hold the two k-halves of column l % 32
 #pragma unroll
-        for (int j = 0; j < TN; ++j) cs[j] += __shfl_xor(cs[j], 32);
+        for (int j = 0; j < TN; ++j) {
+            cs[j] += __shfl_xor(cs[j], 32);
+            if constexpr (SEG)
+                if (folded) cs[j] = tcs[j] + cs[j];
+        }
         if (do_colsum && lane < 32) {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
@@ -1042,7 +1093,9 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) gemm_dl(GemmArgs args) {
 // One problem at a time left most of the chip to a few tiles (the o and qkv
 // gradients of a d_model 1024 layer have 64 and 192 tiles, and at d_model 512
 // none has more than 64); together they fill it, in one launch.  (D = 512, F =
-// 2048, 1024 rows: four launches of 21.6 us each, now one.)
+// 2048, 1024 rows: four launches of 21.6 us each, now one.)  A reduction that its
+// own launch would split is added up in the same segments (SEG), so grouping
+// changes no bit.
 constexpr int MAX_GROUP = 8;
 struct GemmGroup {
     int n;
@@ -1057,7 +1110,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_dw_group(GemmGroup g) {
     const GemmArgs& a = g.a[i];
     int tm, tn;
     band_tile(id - g.start[i], (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, band_rows<BM, BN, NSTAGE>(gridDim.x), tm, tn);
-    gemm_dl_tile<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, false, false, 1, false, RAG>(a, tm, tn, 0, 1);
+    gemm_dl_tile<BM, BN, WM, WN, NSTAGE, EPI_ACC_F32, 0, false, false, 1, false, RAG, true>(a, tm, tn, 0, 1);
 }
 
 // Sum the split-K partials in split order and apply the epilogue; 4 columns
@@ -1598,6 +1651,9 @@ gp_status gemm_dw_group(const GemmArgs* a, int n, hipStream_t st) {
         gp_status s = check_args<bf16>(a[i], false, false);
         if (s != GP_OK) return s;
         g.a[i] = a[i];
+        int cfg, splits;
+        decide_bf16(a[i], EPI_ACC_F32, false, cfg, splits);
+        g.a[i].seg = ((a[i].K + 63) / 64 + splits - 1) / splits;
         g.start[i + 1] = g.start[i] + ((a[i].M + 127) / 128) * ((a[i].N + 127) / 128);
         rag = rag || a[i].K % 64;
     }

@@ -55,11 +55,13 @@ struct GemmArgs {
     // A and B hold fp16 values instead of bf16 (EPI_STORE, k-contiguous, no
     // fp4 term); the tile and split choice is the bf16 one
     int f16 = 0;
+    int seg = 0;  // gemm_dw_group's own: k-tiles of 64 per partial sum
 };
 
 gp_status gemm(const GemmArgs& a, int epi, bool a_kmajor, bool b_kmajor, int dtype, hipStream_t st);
 // n (<= 8) bf16 weight-gradient GEMMs (EPI_ACC_F32, m/n-contiguous operands,
-// column sums as asked for) in one launch; no split-K.
+// column sums as asked for) in one launch.  Not split over workgroups, but a
+// reduction that gemm() would split is added up in the same parts: the same bits.
 gp_status gemm_dw_group(const GemmArgs* a, int n, hipStream_t st);
 // The fp32 GEMM (gemm_f32.hip), operands of one majorness (k_major: both
 // k-contiguous); no split-K: ws is not used.  Arguments checked by gemm().

@@ -49,6 +49,22 @@ CASES = [
     _cfg("xent%d" % v, layers=1, batch=6, loss="xent_ls", vocab=v, label_smoothing=0.1, logit_clip=c)
     for v, c in ((64, 0.0), (264, 0.3), (2048, 0.3), (2112, 0.0), (4160, 0.3), (8256, 0.0), (16448, 0.0), (32000, 0.0),
                  (32768, 0.3))
+] + [
+    # weight gradients whose single launches split the reduction over rows, accumulated over pairs
+    _cfg("dw_split", d_model=1024, heads=16, d_ff=1024, seq=256, batch=32, micro=4),
+    _cfg("dw_split_odd", layers=1, d_model=512, heads=8, d_ff=512, seq=256, batch=24, micro=3),
+    _cfg("dw_split_decoder", layers=1, d_model=512, heads=8, d_ff=512, seq=256, mem_seq=128, batch=32, micro=2,
+         kind="decoder"),
+    _cfg("dw_split768", layers=1, d_model=768, heads=12, d_ff=768, seq=192, batch=24, micro=2),
+    # reductions that are no multiple of 64: over widths, over rows, over both; split and not
+    _cfg("rag", d_model=320, heads=5, d_ff=1000, seq=96, batch=15, micro=5, loss="mse"),
+    _cfg("rag_wide", d_model=512, heads=8, d_ff=2056, batch=2, micro=2),
+    _cfg("rag_rows", layers=1, d_model=256, heads=4, d_ff=520, seq=96, batch=21, micro=1),
+    _cfg("rag_decoder", d_model=256, heads=4, d_ff=1000, seq=96, mem_seq=32, batch=21, micro=1, kind="decoder",
+         loss="xent_ls", vocab=1000, label_smoothing=0.1),
+    _cfg("rag_tiles", layers=1, d_model=1024, heads=16, d_ff=8200, seq=224, batch=3, micro=1),
+    _cfg("rag_head", layers=1, loss="xent_ls", vocab=8200, label_smoothing=0.1, logit_clip=0.3),
+    _cfg("rag_m3", layers=1, d_model=128, heads=2, d_ff=264, seq=224, batch=9, micro=3),
 ]
 
 
