@@ -859,6 +859,32 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
     float cs[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) cs[j] = 0.f;
+    // Ragged K: a share per four k-rows of every k-tile (rows 16 s + 8 h + 4 q + 0
+    // .. 3: rs[s][q] of half h), summed over the tiles and then in row order, as
+    // the register-staged kernel adds them.
+    const bool do_rs = RAG && COLSUM && args.K % 64 != 0;
+    float rs[RAG && COLSUM ? TN : 1][KS][2] = {};
+    // this lane's column sums of the k-tiles so far, both halves of the wave
+    auto colsums = [&](int j) {
+        if constexpr (RAG && COLSUM) {
+            if (do_rs) {
+                float t = 0.f;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const float o0 = __shfl_xor(rs[j][s][0], 32), o1 = __shfl_xor(rs[j][s][1], 32);
+                    t += h ? o0 : rs[j][s][0];
+                    t += h ? o1 : rs[j][s][1];
+                    t += h ? rs[j][s][0] : o0;
+                    t += h ? rs[j][s][1] : o1;
+                    rs[j][s][0] = rs[j][s][1] = 0.f;
+                }
+                return t;
+            }
+        }
+        const float t = cs[j] + __shfl_xor(cs[j], 32);
+        cs[j] = 0.f;
+        return t;
+    };
 
     // SEG: the segments before this one
     f32x16 tot[SEG ? TM : 1][SEG ? TN : 1];
@@ -878,9 +904,8 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
                     }
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const float c = cs[j] + __shfl_xor(cs[j], 32);
+                const float c = colsums(j);
                 tcs[j] = folded ? tcs[j] + c : c;
-                cs[j] = 0.f;
             }
             folded = true;
         }
@@ -925,7 +950,11 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
 #pragma unroll
                             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                                for (int e = 0; e < 8; ++e) cs[j] += (float)fb[cur][j].v[e];
+                                for (int e = 0; e < 8; ++e)
+                                    if (RAG && do_rs)
+                                        rs[RAG ? j : 0][s][e >> 2] += (float)fb[cur][j].v[e];
+                                    else
+                                        cs[j] += (float)fb[cur][j].v[e];
                         }
                     }
                     if (s + 1 < KS) {
@@ -1025,7 +1054,7 @@ __device__ __forceinline__ void gemm_dl_tile(const GemmArgs& args, int tm, int t
         // lanes l and l + 32 hold the two k-halves of column l % 32
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            cs[j] += __shfl_xor(cs[j], 32);
+            cs[j] = colsums(j);
             if constexpr (SEG)
                 if (folded) cs[j] = tcs[j] + cs[j];
         }
@@ -1154,7 +1183,9 @@ __global__ void __launch_bounds__(256) splitk_reduce(GemmArgs args, int splits) 
 // checks): thread t of a block owns columns 4 t .. 4 t + 3 of a 1024-column
 // chunk (blockIdx.x) over `rows` consecutive rows (blockIdx.y), so no index
 // division is needed and each row of partials is read as whole 4 KB runs.
-template <int EPI>
+// RAG (the reduction was no multiple of 64): EPI_RES_F32 adds the residual and
+// then the bias, as splitk_reduce does, instead of their sum.
+template <int EPI, bool RAG = false>
 __global__ void __launch_bounds__(256) splitk_reduce_v4(GemmArgs args, int splits, int rows) {
     const int col = blockIdx.x * 1024 + threadIdx.x * 4;
     if (col >= args.N) return;
@@ -1185,7 +1216,8 @@ __global__ void __launch_bounds__(256) splitk_reduce_v4(GemmArgs args, int split
                 for (int j = 0; j < 4; ++j) s[j] = fmaxf(s[j], 0.f);
             *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(args.C) + i) = {(bf16)s[0], (bf16)s[1], (bf16)s[2], (bf16)s[3]};
         } else if constexpr (EPI == EPI_RES_F32) {
-            s += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(args.aux) + (long)row * args.ldaux + col) + bv;
+            const f32x4 x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(args.aux) + (long)row * args.ldaux + col);
+            s = RAG ? (s + x) + bv : s + (x + bv);
             *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(args.C) + i) = s;
             if (args.C2)
                 *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(args.C2) + (long)row * args.ldc2 + col) =
@@ -1220,7 +1252,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 // The split-K reduce of a bf16 GEMM: 16-byte accesses when every operand of
 // the epilogue allows them, element accesses otherwise.
-gp_status launch_reduce(const GemmArgs& a, int epi, int splits, hipStream_t st) {
+gp_status launch_reduce(const GemmArgs& a, int epi, int splits, hipStream_t st, bool rag = false) {
     const bool res = epi == EPI_RES_F32, mask = epi == EPI_RELU_MASK;
     const bool v4 = a.N % 4 == 0 && a.ldc % 4 == 0 && aligned16(a.C) && aligned16(a.ws) &&
                     (!(epi == EPI_STORE || res) || !a.bias || aligned16(a.bias)) &&
@@ -1234,7 +1266,12 @@ gp_status launch_reduce(const GemmArgs& a, int epi, int splits, hipStream_t st) 
         const dim3 grid(cx, (a.M + rows - 1) / rows);
         switch (epi) {
         case EPI_STORE: klaunch(splitk_reduce_v4<EPI_STORE>, grid, 256, 0, st, a, splits, rows); break;
-        case EPI_RES_F32: klaunch(splitk_reduce_v4<EPI_RES_F32>, grid, 256, 0, st, a, splits, rows); break;
+        case EPI_RES_F32:
+            if (rag)
+                klaunch(splitk_reduce_v4<EPI_RES_F32, true>, grid, 256, 0, st, a, splits, rows);
+            else
+                klaunch(splitk_reduce_v4<EPI_RES_F32>, grid, 256, 0, st, a, splits, rows);
+            break;
         case EPI_F32: klaunch(splitk_reduce_v4<EPI_F32>, grid, 256, 0, st, a, splits, rows); break;
         case EPI_RELU_MASK: klaunch(splitk_reduce_v4<EPI_RELU_MASK>, grid, 256, 0, st, a, splits, rows); break;
         case EPI_ACC_F32: klaunch(splitk_reduce_v4<EPI_ACC_F32>, grid, 256, 0, st, a, splits, rows); break;
@@ -1298,11 +1335,11 @@ gp_status launch_dl(const GemmArgs& a, int epi, int splits, hipStream_t st) {
         dim3 grid(tiles, splits);
         klaunch(gemm_dl<BM, BN, WM, WN, NSTAGE, EPI_F32, 1, KM, false, 1, false, RAG>, grid, NT, 0, st, a);
         GP_LAUNCH_CHECK();
-        if (a.deferred && (epi == EPI_RES_F32 || epi == EPI_F32)) {
+        if (a.deferred && ((epi == EPI_RES_F32 && !RAG) || epi == EPI_F32)) {
             *a.deferred = splits;  // the caller reduces
             return GP_OK;
         }
-        return launch_reduce(a, epi, splits, st);
+        return launch_reduce(a, epi, splits, st, RAG);
     }
     if constexpr (KM) {
         switch (epi) {
@@ -1500,6 +1537,31 @@ double split_weight() {
 
 void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& splits);
 
+// Splits of a reduction that is no multiple of 64: the cost of 128 x 128 x 64
+// steps (two co-resident tiles hide each other's latencies: 1.5 times, not twice,
+// the time of one), plus the partial-tile traffic at about 1.75 TB/s and the
+// reduce's launch (one unit = one step of a lone tile, 0.58 us).  The split count
+// fixes the order an element's products are added in, so it depends on the problem
+// alone and not on the tile it runs on: the rule is that of the register-staged
+// 128 x 128 tile such problems had first, and their results keep its bits.
+int rag_splits(const GemmArgs& a) {
+    const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    const int nk = (a.K + 63) / 64;
+    double best = 1e300;
+    int splits = 1;
+    for (int s = 1; s <= 8; s *= 2) {
+        if (s > 1 && !split_fits(a, s, nk)) continue;
+        const long wgs = tiles * s, rounds = (wgs + 2 * NUM_CU - 1) / (2 * NUM_CU);
+        double t = rounds * (wgs > NUM_CU ? 1.5 : 1.0) * (double)((nk + s - 1) / s);
+        if (s > 1) t += (double)a.M * a.N * 4.0 * (s + 1.0) / 2.0 / 1.0e6 + 4.0;
+        if (t < best * 0.999) {
+            best = t;
+            splits = s;
+        }
+    }
+    return splits;
+}
+
 // Shapes instantiated for a K that is no multiple of 64 (widths like 1000, odd
 // token counts): one for few output tiles and one for many.
 bool rag_capable(int cfg, bool kmaj) {
@@ -1557,6 +1619,7 @@ void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& split
     // three times over for them.
     const double split_w = (kmaj ? 1.0 : 3.0) * split_weight();
     const int nk = (a.K + 63) / 64;
+    const int rs = a.K % 64 ? rag_splits(a) : 0;  // ragged: only the shape is open
     double best = 1e300;
     cfg = T_DL128x128_W8A;
     splits = 1;
@@ -1565,7 +1628,7 @@ void choose_dl_model(const GemmArgs& a, int epi, bool kmaj, int& cfg, int& split
         if (mx && !mx_capable(c.cfg)) continue;
         if (a.K % 64 && !rag_capable(c.cfg, kmaj)) continue;
         const long tiles = (long)((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
-        for (int s = 1; s <= 4; s *= 2) {
+        for (int s = rs ? rs : 1; s <= (rs ? rs : 4); s *= 2) {
             if (s > 1 && !split_fits(a, s, nk)) continue;
             const long per_cu = (tiles * s + NUM_CU - 1) / NUM_CU;
             const long rounds = (per_cu + c.resident - 1) / c.resident;
