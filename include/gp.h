@@ -26,7 +26,11 @@
  *    buffers owned by the caller; the library never frees them.  The library
  *    owns its parameters, gradient accumulators, stash and workspaces, which it
  *    allocates in gp_partition_configure and frees in gp_partition_destroy;
- *    nothing is allocated on the per-micro-batch path.
+ *    no memory is allocated on the per-micro-batch path.  The two streams of
+ *    its own that a mini-batch uses come from a pool per device; the last
+ *    forward or the first backward of a mini-batch creates them only where
+ *    every pair is inside another partition's mini-batch, or recording into
+ *    another capture, at that moment.
  *  - "Partition dtype" (gp_config.dtype) is the element type of boundary
  *    tensors: float32 (GP_F32) or bfloat16 (GP_BF16, bf16 GEMM operands with
  *    fp32 accumulation; the residual stream, LayerNorm statistics, softmax,
@@ -233,7 +237,8 @@ gp_status gp_forward_microbatch(gp_partition* p, int mb, const void* x, const vo
  * GEMMs go to a static device array of the library (32 MiB, one per device,
  * held until the process ends) instead of the partition's workspace; it does
  * not start the early recompute of the last micro-batch (that backward then
- * recomputes on its own stream).  Every call on a device shares the array:
+ * recomputes on its own stream), and it takes and creates none of the
+ * library's streams.  Every call on a device shares the array:
  * calls that overlap on one device (two streams, two host threads) race; on
  * one partition each of these calls waits for the previous forward in both
  * first-pass workspaces, so they never overlap each other.

@@ -161,23 +161,22 @@ using namespace gp;
 // The library's two streams of a mini-batch (weight gradients, recompute).
 // HIP maps streams onto four hardware queues and two busy streams on one queue
 // run one after the other, so partitions do not keep streams of their own: a
-// partition takes a pair with the first forward of a mini-batch and gives it
-// back with the step, and a process that steps several partitions in turn runs
-// them all on the one pair its caller's streams leave room for.  (With a pair
-// per partition and three partitions alive, those after the first shared
-// queues with the caller's streams: 8 layers of width 512 took 9.9 ms a step
-// and take 7.6, a 2-layer decoder with its head 23.6 and 20.6.)
-// Partitions inside a mini-batch at the same time, from one thread or several,
-// each hold their own pair, so the pool never has more pairs than that, and
-// the last partition of a device destroys them.  A pair whose streams are
-// recording into a capture goes only to a call of that capture.
-struct StreamPair {
-    hipStream_t side = nullptr, remat = nullptr;
-};
-struct StreamPool {
+// partition takes a pair with the first call of a mini-batch that uses one (the
+// last forward where it starts the early recompute, else the first backward) and
+// gives it back with the step, and a process that steps several partitions in turn
+// runs them all on the one pair its caller's streams leave room for.  (With a pair
+// per partition and three partitions alive, those after the first shared queues
+// with the caller's streams: 8 layers of width 512 took 9.9 ms a step and take 7.6,
+// a 2-layer decoder with its head 23.6 and 20.6.)
+// Partitions inside a mini-batch at the same time, from one thread or several, each
+// hold their own pair, created when there is none idle.  A pair whose streams are
+// recording into a capture goes only to a call of that capture, so there are at
+// most as many pairs as partitions inside a mini-batch at once plus captured steps
+// whose capture was open meanwhile; the pairs beyond one per partition go when a
+// partition does, all with the device's last.
+typedef PairPool<hipStream_t>::Pair StreamPair;
+struct StreamPool : PairPool<hipStream_t> {
     std::mutex mu;
-    std::vector<StreamPair> idle;  // last given back, first taken
-    int partitions = 0;
 };
 constexpr int POOL_DEVICES = 64;
 static StreamPool& stream_pool(int dev) {
@@ -377,7 +376,7 @@ struct gp_partition {
     hipStream_t remat = nullptr;      // side and remat: held during a mini-batch (StreamPool)
     int pool_dev = -1;                // the device whose pool this partition uses (-1: not configured)
     bool streams_held = false;
-    hipStream_t pair_side = nullptr, pair_remat = nullptr;  // the pair taken (side and remat: those in use)
+    StreamPair pair;                  // the pair taken (side and remat: those in use)
     hipEvent_t remat_done = nullptr;  // from evring
     int remat_pending = -1;  // micro-batch whose recompute-ahead is enqueued
 
@@ -1369,34 +1368,40 @@ gp_status create_pair(StreamPair& s) {
     return GP_OK;
 }
 
-// Take a pair of streams for the mini-batch that begins on `st`.
+// Whether a stream is recording into a capture other than `cap` (an invalidated
+// capture is nobody's until its owner ends it).
+bool recording_elsewhere(hipStream_t st, unsigned long long cap) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(st, &cs, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone && !(cs == hipStreamCaptureStatusActive && id == cap);
+}
+
+// Take a pair of streams for the mini-batch, for a call on `st`.
 gp_status take_streams(gp_partition* p, hipStream_t st) {
     if (p->streams_held || (!p->use_side && !p->ahead())) return GP_OK;
     StreamPool& pool = stream_pool(p->pool_dev);
+    std::lock_guard<std::mutex> lock(pool.mu);
+    const unsigned long long cap = capture_of(st);
+    gp_status s = GP_OK;
     StreamPair got;
-    {
-        std::lock_guard<std::mutex> lock(pool.mu);
-        const unsigned long long cap = capture_of(st);
-        for (size_t i = pool.idle.size(); i-- > 0 && !got.side;) {
-            const StreamPair s = pool.idle[i];
-            const unsigned long long a = capture_of(s.side), b = capture_of(s.remat);
-            if ((a && a != cap) || (b && b != cap)) continue;
-            got = s;
-            pool.idle.erase(pool.idle.begin() + (long)i);
-        }
-    }
-    if (!got.side) {
-        int dev = 0;
-        GP_HIP(hipGetDevice(&dev));
-        if (dev != p->pool_dev) GP_HIP(hipSetDevice(p->pool_dev));
-        const gp_status s = create_pair(got);
-        if (dev != p->pool_dev) (void)hipSetDevice(dev);
-        if (s != GP_OK) return s;
-    }
+    pool.take(
+        got, [&](const StreamPair& x) { return recording_elsewhere(x.side, cap) || recording_elsewhere(x.remat, cap); },
+        [&](StreamPair& x) {
+            int dev = 0;
+            hipError_t e = hipGetDevice(&dev);
+            if (e == hipSuccess && dev != p->pool_dev) e = hipSetDevice(p->pool_dev);
+            s = e == hipSuccess ? create_pair(x) : hip_fail(e, __FILE__, __LINE__);
+            if (dev != p->pool_dev) (void)hipSetDevice(dev);
+            return s == GP_OK;
+        });
+    if (s != GP_OK) return s;
     p->side = p->use_side ? got.side : nullptr;
     p->remat = p->ahead() ? got.remat : nullptr;
-    p->pair_side = got.side;
-    p->pair_remat = got.remat;
+    p->pair = got;
     p->streams_held = true;
     return GP_OK;
 }
@@ -1407,8 +1412,8 @@ void give_streams(gp_partition* p) {
     if (!p->streams_held) return;
     StreamPool& pool = stream_pool(p->pool_dev);
     std::lock_guard<std::mutex> lock(pool.mu);
-    pool.idle.push_back({p->pair_side, p->pair_remat});
-    p->side = p->remat = p->pair_side = p->pair_remat = nullptr;
+    pool.give(p->pair);
+    p->side = p->remat = nullptr;
     p->streams_held = false;
 }
 
@@ -1422,13 +1427,11 @@ void free_all(gp_partition* p) {
     if (p->pool_dev >= 0) {
         StreamPool& pool = stream_pool(p->pool_dev);
         std::lock_guard<std::mutex> lock(pool.mu);
-        if (--pool.partitions == 0) {
-            for (const StreamPair& s : pool.idle) {
-                (void)hipStreamDestroy(s.side);
-                (void)hipStreamDestroy(s.remat);
-            }
-            pool.idle.clear();
-        }
+        pool.remove([](const StreamPair& s) { return recording_elsewhere(s.side, 0) || recording_elsewhere(s.remat, 0); },
+                    [](const StreamPair& s) {
+                        (void)hipStreamDestroy(s.side);
+                        (void)hipStreamDestroy(s.remat);
+                    });
         p->pool_dev = -1;
     }
     p->remat_done = nullptr;
@@ -1718,22 +1721,14 @@ gp_status gp_partition_configure(gp_partition* p, const gp_config* cfg) {
             return s;
         }
     }
-    // the device's first partition creates the first pair, outside any capture
+    // the device's first partition creates the first pair of streams
     int pool_dev = 0;
     e = hipGetDevice(&pool_dev);
     if (e == hipSuccess && (pool_dev < 0 || pool_dev >= POOL_DEVICES)) e = hipErrorInvalidDevice;
-    if (e == hipSuccess) {
+    if (e == hipSuccess && (p->use_side || p->ahead())) {
         StreamPool& pool = stream_pool(pool_dev);
         std::lock_guard<std::mutex> lock(pool.mu);
-        StreamPair first;
-        if (pool.partitions == 0 && (p->use_side || p->ahead())) {
-            s = create_pair(first);
-            if (s == GP_OK) pool.idle.push_back(first);
-        }
-        if (s == GP_OK) {
-            ++pool.partitions;
-            p->pool_dev = pool_dev;
-        }
+        if (pool.add([&](StreamPair& n) { return (s = create_pair(n)) == GP_OK; })) p->pool_dev = pool_dev;
     }
     if (s != GP_OK) {
         free_all(p);
@@ -1877,7 +1872,6 @@ gp_status gp_forward_microbatch(gp_partition* p, int mb, const void* x, const vo
     if (dec && !mem) return set_error(GP_ERR_INVALID_ARG, "decoder partitions need the memory input");
     if (!dec && mem) return set_error(GP_ERR_INVALID_ARG, "encoder partitions take no memory input");
     const int lane = p->lane_of(mb);
-    GP_TRY(take_streams(p, (hipStream_t)stream));
     Ctx c = first_pass_ctx(p, (hipStream_t)stream, lane);
     GP_TRY(order_first_pass(p, c, false));
     const int set = p->g.keep_act ? p->set_of(mb) : 0;
@@ -1905,6 +1899,7 @@ gp_status gp_forward_microbatch(gp_partition* p, int mb, const void* x, const vo
         GP_HIP(hipEventRecord(f.stashed, c.st));
     }
     if (early_on && mb == p->g.M - 1) {
+        GP_TRY(take_streams(p, c.st));
         const hipEvent_t fork = p->next_event();
         GP_HIP(hipEventRecord(fork, c.st));
         Ctx cr = make_ctx(p, p->remat, Lane::Remat);
@@ -1950,7 +1945,6 @@ gp_status gp_forward_microbatch_noalloc(gp_partition* p, int mb, const void* x, 
     // so this pass also waits for the other slot's last forward (two of these
     // in flight would share the array).
     const int lane = p->lane_of(mb);
-    GP_TRY(take_streams(p, (hipStream_t)stream));
     Ctx c = first_pass_ctx(p, (hipStream_t)stream, lane);
     c.ws = p->noalloc_scratch;
     GP_TRY(order_first_pass(p, c, true));
@@ -1985,6 +1979,7 @@ gp_status gp_backward_microbatch_remat(gp_partition* p, int mb, const void* dy_o
     if (!dec && dmem) return set_error(GP_ERR_INVALID_ARG, "encoder partitions have no memory gradient");
     const bool lanes = p->bwd_lanes > 1;
     const int bl = p->blane(mb);
+    GP_TRY(take_streams(p, (hipStream_t)stream));
     Ctx c = make_ctx(p, (hipStream_t)stream);
     c.last = mb == 0;
     if (bl) {

@@ -101,6 +101,58 @@ inline gp_status check_config(const Dims& d, const gp_config& c, std::string& ms
     return GP_OK;
 }
 
+// -------------------------------------------------------------- stream pairs
+// The pool of the library's stream pairs on one device: which pair a mini-batch
+// takes and when one is created or destroyed (see partition.hip).
+template <class Stream> struct PairPool {
+    struct Pair {
+        Stream side{}, remat{};
+    };
+    std::vector<Pair> idle;  // last given back, first taken
+    int partitions = 0;      // that use streams
+    int pairs = 0;           // idle or held
+
+    // A new partition; the first one creates the first pair.  create(Pair&): success.
+    template <class Create> bool add(Create&& create) {
+        if (pairs == 0) {
+            Pair p;
+            if (!create(p)) return false;
+            idle.push_back(p);
+            ++pairs;
+        }
+        ++partitions;
+        return true;
+    }
+    // The pair for a mini-batch: the last one given back that is not recording into
+    // another capture (elsewhere(Pair)), else a new one.
+    template <class Elsewhere, class Create> bool take(Pair& out, Elsewhere&& elsewhere, Create&& create) {
+        for (size_t i = idle.size(); i-- > 0;) {
+            if (elsewhere(idle[i])) continue;
+            out = idle[i];
+            idle.erase(idle.begin() + (long)i);
+            return true;
+        }
+        if (!create(out)) return false;
+        ++pairs;
+        return true;
+    }
+    void give(const Pair& p) { idle.push_back(p); }
+    // A partition is gone: idle pairs beyond one per partition go with it (a
+    // recording one waits for a later call), with the last partition all.
+    template <class Recording, class Destroy> void remove(Recording&& recording, Destroy&& destroy) {
+        --partitions;
+        for (size_t i = 0; i < idle.size() && pairs > partitions;) {
+            if (partitions > 0 && recording(idle[i])) {
+                ++i;
+                continue;
+            }
+            destroy(idle[i]);
+            idle.erase(idle.begin() + (long)i);
+            --pairs;
+        }
+    }
+};
+
 // ------------------------------------------------------------ parameter plan
 // fp32 masters and gradients share one layout.  A linear layer stores W as
 // [in, out] row-major immediately followed by its bias [out]; a LayerNorm

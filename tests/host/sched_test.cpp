@@ -126,6 +126,36 @@ int main() {
     CHECK(s.can_step(msg) == GP_OK, "sched_step_ready");
     s.did_step();
     CHECK(s.can_set_param(msg) == GP_OK && s.can_forward(0, msg) == GP_OK, "sched_next_minibatch");
+    // ---- stream pairs (streams are numbers)
+    typedef PairPool<int> Pool;
+    Pool pool;
+    int made = 0, destroyed = 0, captured = 0;  // captured: the pair recording into a capture
+    auto create = [&](Pool::Pair& q) { q.side = ++made; q.remat = -made; return true; };
+    auto destroy = [&](const Pool::Pair&) { ++destroyed; };
+    auto elsewhere = [&](const Pool::Pair& q) { return q.side == captured; };
+    pool.add(create); pool.add(create); pool.add(create);
+    CHECK(made == 1 && pool.pairs == 1, "pool_first_partition_creates_the_first_pair");
+    Pool::Pair a, b, c2;
+    bool one = true;
+    for (int i = 0; i < 6; ++i) {
+        one = one && pool.take(a, elsewhere, create) && a.side == 1;
+        pool.give(a);
+    }
+    CHECK(one && made == 1, "pool_steps_in_turn_on_one_pair");
+    CHECK(pool.take(a, elsewhere, create) && pool.take(b, elsewhere, create) && a.side == 1 && b.side == 2 &&
+              pool.pairs == 2, "pool_pairs_of_their_own_inside_mini_batches");
+    pool.give(b); pool.give(a);
+    captured = 1;
+    CHECK(pool.take(c2, elsewhere, create) && c2.side == 2 && made == 2, "pool_skips_a_recording_pair");
+    pool.give(c2);
+    pool.remove(elsewhere, destroy);
+    CHECK(destroyed == 0 && pool.pairs == 2, "pool_keeps_a_pair_per_partition");
+    pool.remove(elsewhere, destroy);
+    CHECK(destroyed == 1 && pool.pairs == 1 && pool.idle[0].side == 1, "pool_shrinks_past_a_recording_pair");
+    pool.remove(elsewhere, destroy);
+    CHECK(destroyed == 2 && pool.pairs == 0 && pool.idle.empty(), "pool_empty_with_the_last");
+    auto none = [&](Pool::Pair&) { return false; };
+    CHECK(!pool.add(none) && pool.partitions == 0 && pool.pairs == 0, "pool_failed_creation_adds_nothing");
     std::printf("%d failures\n", fails);
     return fails ? 1 : 0;
 }

@@ -131,3 +131,39 @@ def test_capture_while_another_partition_is_inside_a_mini_batch():
     b.part.close()
     _same(ra, _alone(1, 2))
     _same(rb, _alone(2, 3))
+
+
+def test_noalloc_forwards_while_another_partition_is_inside_a_mini_batch():
+    """The other partition holds the idle pair of streams: the no-allocation
+    forwards take none (they would have to create one), the backward does."""
+    from paper_1811_06965_amd import gp
+    st = torch.cuda.current_stream().cuda_stream
+    a, b = Run(1), Run(2)
+    a.forwards(st)
+    for m, (x, y) in enumerate(zip(b._chunks(b.inp["x"]), b._chunks(b.y))):
+        gp.gp_forward_microbatch_noalloc(b.part.h, m, x, None, y, st)
+    b.backwards(st)
+    a.backwards(st)
+    a.update(st)
+    b.update(st)
+    ra, rb = a.result(), b.result()
+    a.part.close()
+    b.part.close()
+    _same(ra, _alone(1, 1))
+    _same(rb, _alone(2, 1))
+
+
+def test_partitions_in_turn_on_streams_of_their_own():
+    runs = [Run(s) for s in (1, 2)]
+    streams = [torch.cuda.Stream() for _ in runs]
+    for _ in range(3):
+        for r, st in zip(runs, streams):
+            r.steps(1, st.cuda_stream)
+    got = [r.result() for r in runs]
+    runs[0].part.close()  # its pair goes, the other partition's stays
+    runs[1].steps(1, streams[0].cuda_stream)
+    last = runs[1].result()
+    runs[1].part.close()
+    for s, g in zip((1, 2), got):
+        _same(g, _alone(s, 3))
+    _same(last, _alone(2, 4))
