@@ -20,10 +20,14 @@
 // workgroup are few.  Each result equals, bit for bit, that of the form this
 // replaced -- a wave per row with scalar fma chains, every lane reading whole
 // K and V rows from memory: at 4 x 8 heads of 128 x 64, in a step, forward 45.5
-// -> 13.7 us, dQ 55.9 -> 20.7, dK/dV 77.2 -> 19.5.
+// -> 13.7 us, dQ 55.9 -> 20.7, dK/dV 77.2 -> 19.5.  That includes infinities and
+// NaN behind the causal mask: a product's 16 x 16 block on the diagonal multiplies
+// them by the masked scores' zeros, so where such a block holds any, its chain
+// leaves the masked products out one by one (masked_block).
 //
 // bf16 partitions use the MFMA kernels in attention_mfma.hip.
 #include "common.hpp"
+#include "gemm_tile.hpp"
 #include "kernels.hpp"
 
 namespace gp {
@@ -84,27 +88,70 @@ __device__ __forceinline__ f32x4 block_dot(const float* a, const float* b) {
 // fall in distinct banks.
 constexpr int srow(int SB) { return SB + 4; }
 
+// This lane's column of the rows of X: element k is row k's, zero from row n on
+// (out of the buffer's range).
+struct XCol {
+    Rsrc r;
+    uint32_t off, ld;  // bytes
+    __device__ __forceinline__ float operator[](int k) const {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off + k * ld, 0, 0));
+    }
+};
+__device__ __forceinline__ XCol x_col(const float* X, long ld, int n, int dh, int col) {
+    return {make_rsrc(X, (uint32_t)(((long)(n - 1) * ld + dh) * 4)), (uint32_t)min(col, dh - 1) * 4, (uint32_t)ld * 4};
+}
+
 // sum over k in [k0, k1) of P[16][k] X[k][col] (k0 a multiple of 4): lane's
-// score row lane % 16, X rows ld apart, this lane's column at x.  P is zero
-// from k1 to the next multiple of 4.  X does not depend on the scores: the
-// first 4 NPRE rows are loaded before they are ready (prefetch_rows).
+// score row lane % 16, this lane's column of X, whose rows end at k1.  P is zero
+// from k1 to the next multiple of 4.  X does not depend on the scores: the first
+// 4 NPRE rows are loaded before they are ready (prefetch_rows).
 constexpr int NPRE = 32;
-__device__ __forceinline__ void prefetch_rows(const float* x, long ld, int k0, int k1, int lane, float* pre) {
+__device__ __forceinline__ void prefetch_rows(const XCol& x, int k0, int k1, int lane, float* pre) {
 #pragma unroll
     for (int i = 0; i < NPRE; ++i) {
         pre[i] = 0.f;
-        if (k0 + 4 * i < k1) pre[i] = x[(long)min(k0 + 4 * i + (lane >> 4), k1 - 1) * ld];
+        if (k0 + 4 * i < k1) pre[i] = x[k0 + 4 * i + (lane >> 4)];
     }
 }
 template <int SB>
-__device__ __forceinline__ f32x4 chain(const float* P, const float* x, long ld, int k0, int k1, int lane, const float* pre) {
+__device__ __forceinline__ f32x4 chain(const float* P, const XCol& x, int k0, int k1, int lane, const float* pre) {
     f32x4 c = {0.f, 0.f, 0.f, 0.f};
     const float* p = P + (lane & 15) * srow(SB) + (lane >> 4);
 #pragma unroll
     for (int i = 0; i < NPRE; ++i)
         if (k0 + 4 * i < k1) c = mma4(p[k0 + 4 * i], pre[i], c);
 #pragma unroll 16
-    for (int k = k0 + 4 * NPRE; k < k1; k += 4) c = mma4(p[k], x[(long)min(k + (lane >> 4), k1 - 1) * ld], c);
+    for (int k = k0 + 4 * NPRE; k < k1; k += 4) c = mma4(p[k], x[k + (lane >> 4)], c);
+    return c;
+}
+// Whether any X row of the diagonal block [d, d + 16) holds an infinity or a NaN
+// in the wave's columns (the same answer in every lane).
+__device__ __forceinline__ bool masked_block(const XCol& x, int d, int lane) {
+    bool bad = false;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) bad = bad || !(fabsf(x[d + 4 * t + (lane >> 4)]) < INFINITY);
+    return __any(bad);
+}
+// The same sum where masked_block holds: of the block's columns, row r of the 16
+// takes only d .. d + r (UPTO) or d + r .. d + 15, as scalar fma chains in the same
+// order.
+template <int SB, bool UPTO>
+__device__ __forceinline__ f32x4 chain_masked(const float* P, const XCol& x, int k0, int k1, int d, int lane) {
+    f32x4 c = {0.f, 0.f, 0.f, 0.f};
+    const float* p = P + (lane & 15) * srow(SB) + (lane >> 4);
+#pragma unroll 1
+    for (int k = k0; k < d; k += 4) c = mma4(p[k], x[k + (lane >> 4)], c);
+#pragma unroll 1
+    for (int k = d; k < min(d + 16, k1); ++k) {
+        const float v = x[k];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * (lane >> 4) + r;
+            if (UPTO ? k - d <= row : k - d >= row) c[r] = __builtin_fmaf(P[row * srow(SB) + k], v, c[r]);
+        }
+    }
+#pragma unroll 1
+    for (int k = d + 16; k < k1; k += 4) c = mma4(p[k], x[k + (lane >> 4)], c);
     return c;
 }
 
@@ -143,9 +190,9 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
         for (int r = 0; r < 4; ++r) ps[(4 * (lane >> 4) + r) * srow(SB) + kb + (lane & 15)] = a.scale * c[r];
     }
     const int col = w * 16 + (lane & 15);
-    const float* x = V + min(col, a.dh - 1);
+    const XCol x = x_col(V, a.ldv, len, a.dh, col);
     float pre[NPRE];
-    prefetch_rows(x, a.ldv, 0, len, lane, pre);
+    prefetch_rows(x, 0, len, lane, pre);
     __syncthreads();
     {
         // the wave's four rows side by side, so that their reductions overlap
@@ -186,7 +233,8 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
     }
     __syncthreads();
     if (w * 16 >= a.dh) return;
-    const f32x4 o = chain<SB>(ps, x, a.ldv, 0, len, lane, pre);
+    const f32x4 o = a.causal && masked_block(x, pl.r0, lane) ? chain_masked<SB, true>(ps, x, 0, len, pl.r0, lane)
+                                                             : chain<SB>(ps, x, 0, len, lane, pre);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int rr = 4 * (lane >> 4) + r, i = pl.r0 + rr;
@@ -251,12 +299,13 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_f32(AttnArgs a) {
         }
     }
     const int col = w * 16 + (lane & 15);
-    const float* x = K + min(col, a.dh - 1);
+    const XCol x = x_col(K, a.ldk, len, a.dh, col);
     float pre[NPRE];
-    prefetch_rows(x, a.ldk, 0, len, lane, pre);
+    prefetch_rows(x, 0, len, lane, pre);
     __syncthreads();
     if (w * 16 >= a.dh) return;
-    const f32x4 g = chain<SB>(ds, x, a.ldk, 0, len, lane, pre);
+    const f32x4 g = a.causal && masked_block(x, pl.r0, lane) ? chain_masked<SB, true>(ds, x, 0, len, pl.r0, lane)
+                                                             : chain<SB>(ds, x, 0, len, lane, pre);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = pl.r0 + 4 * (lane >> 4) + r;
@@ -301,14 +350,17 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_f32(AttnArgs a) {
             ds[rr * srow(SB) + i] = x;
         }
     }
-    const int col = w * 16 + (lane & 15), cc = min(col, a.dh - 1);
+    const int col = w * 16 + (lane & 15);
+    const XCol xg = x_col(G, a.lddo, a.Sq, a.dh, col), xq = x_col(Q, a.ldq, a.Sq, a.dh, col);
     float pre[NPRE], qpre[NPRE];
-    prefetch_rows(G + cc, a.lddo, first, a.Sq, lane, pre);
-    prefetch_rows(Q + cc, a.ldq, first, a.Sq, lane, qpre);
+    prefetch_rows(xg, first, a.Sq, lane, pre);
+    prefetch_rows(xq, first, a.Sq, lane, qpre);
     __syncthreads();
     if (w * 16 >= a.dh) return;
-    const f32x4 gv = chain<SB>(ps, G + cc, a.lddo, first, a.Sq, lane, pre);
-    const f32x4 gk = chain<SB>(ds, Q + cc, a.ldq, first, a.Sq, lane, qpre);
+    const f32x4 gv = a.causal && masked_block(xg, first, lane) ? chain_masked<SB, false>(ps, xg, first, a.Sq, first, lane)
+                                                               : chain<SB>(ps, xg, first, a.Sq, lane, pre);
+    const f32x4 gk = a.causal && masked_block(xq, first, lane) ? chain_masked<SB, false>(ds, xq, first, a.Sq, first, lane)
+                                                               : chain<SB>(ds, xq, first, a.Sq, lane, qpre);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int j = pl.r0 + 4 * (lane >> 4) + r;

@@ -86,3 +86,33 @@ def test_f32_attention_lengths_and_widths(heads, dh, seq, mem_seq):
                                 micro=1, dtype="f32", kind="decoder" if dec else "encoder", loss="mse")
     case = synth.make_case(cfg, 6, perturb=True)
     _against_oracle(cfg, case, _step(cfg, case))
+
+
+# Infinities and NaN stay on their side of the causal mask, also inside the 16-row
+# block that shares its products: a token's bad input reaches no earlier output, and
+# its bad gradient no later one.  Blocks within the 128 rows that are loaded ahead
+# and beyond them, whole and cut off by the sequence's end, all head-width classes.
+@pytest.mark.parametrize("dh,seq,at", [(64, 40, 21), (12, 40, 37), (32, 36, 32), (48, 204, 149), (64, 1024, 1018)])
+def test_f32_causal_mask_holds_for_nonfinite_values(dh, seq, at):
+    from paper_1811_06965_amd.runtime import Partition
+    cfg = synth.PartitionConfig("mask", layers=1, d_model=2 * dh, d_ff=64, heads=2, seq=seq, mem_seq=8, batch=2, micro=1,
+                                dtype="f32", kind="decoder")
+    case = synth.make_case(cfg, 6, perturb=True)
+    with Partition(cfg) as part:
+        def step(x_at=None, dy_at=None):
+            part.load_params(case["layers"], case["head"])  # a bad gradient leaves bad weights, at any rate
+            inp = part.device_inputs(case)
+            if x_at is not None:
+                inp["x"][0, x_at, 3] = float("inf")
+            if dy_at is not None:
+                inp["dy"][0, dy_at, 5] = float("inf")
+            out = part.step(inp["x"], inp["mem"], inp["dy"])
+            return to_np(out["y"]), to_np(out["dx"])
+        y, dx = step()
+        y_bad, _ = step(x_at=at)
+        _, dx_bad = step(dy_at=at)
+    assert np.isfinite(y).all() and np.isfinite(dx).all()
+    assert not np.isfinite(y_bad[0, at]).any()
+    assert np.array_equal(y[0, :at], y_bad[0, :at]) and np.array_equal(y[1], y_bad[1])
+    assert not np.isfinite(dx_bad[0, at]).any()
+    assert np.array_equal(dx[0, at + 1:], dx_bad[0, at + 1:]) and np.array_equal(dx[1], dx_bad[1])
