@@ -1056,7 +1056,7 @@ gp_status layer_forward(const Ctx& c, int l, LayerWs& w, const float* x_in, floa
     a.o = w.c;
     a.ldo = D;
     a.lse = w.lse;
-GP_TRY(timed_attention(c, GP_K_ATTN_FWD, a, false));
+    GP_TRY(timed_attention(c, GP_K_ATTN_FWD, a, false));
     GP_TRY(linear_fwd(c, P.o, w.c, T, w.x1, D, EPI_RES_F32, 0, x_in, nullptr, nullptr, nullptr, true));
     const float* xf = w.x1;
     if (dec) {
