@@ -355,13 +355,19 @@ struct gp_partition {
     bool use_side = true;
     // When weight-gradient GEMMs are handed to the side stream (GP_DW_FLUSH):
     // -1 (default) as soon as the collected ones have 512 output tiles of 128 x
-    // 128 (two per CU, one round), the rest at the end of the layer; 0 each as
-    // soon as its inputs are enqueued, 1 after the feed-forward block and at
-    // the end of the layer, 2 at the end of the layer.  Collected GEMMs run as
-    // one launch (run_dw_jobs).  ms per step at 0 / -1 / 2: 8 x 512 encoder 7.0
-    // / 6.0 / 6.0; 2-layer decoder with head 20.6 / 19.8 / 19.9; d_model 1024,
-    // M = 8 9.57 / 9.39 / 9.26, M = 32 (whose input-gradient chain waits for
-    // the CUs a large late launch holds) 14.5 / 14.5 / 14.8.
+    // 128 (two per CU, one round) or the layer's last one is in, 0 each as soon as
+    // its inputs are enqueued, 1 after the feed-forward block and at the end of the
+    // layer, 2 at the end of the layer.  Collected GEMMs run as one launch
+    // (run_dw_jobs).  ms per step at 0 / -1, alone in the process: 8 x 512 encoder
+    // 5.73 / 5.40; 4 x 768 stored 4.27 / 3.90; 2-layer decoder with head 20.1 /
+    // 19.2, M = 32 27.0 / 26.4; one d_model 2048 layer 29.1 / 28.5; 16-layer
+    // d_model 1024 encoder M = 4 59.6 / 59.7, M = 8 63.7 / 63.5, M = 16 74.2 /
+    // 74.7, M = 32 99.1 / 99.5 (single launches one by one before: 60.1, 64.3,
+    // 75.5, 100.3).  A rest of fewer than 512 tiles is no faster one by one at any
+    // width tried (512 .. 1408, encoders and decoders).  Handing it over at the
+    // end of the layer instead, behind the input gradient of qkv and the
+    // LayerNorm, leaves the weight-gradient stream idle meanwhile: M = 4 61.2, M =
+    // 32 101.1.
     int dw_flush = -1;
     hipStream_t side = nullptr;
     hipEvent_t side_done[4] = {};  // side stream's last event of layer l % 4 (from evring)
@@ -1248,7 +1254,7 @@ gp_status layer_backward(const Ctx& c, int set, int half, int l, bool first, flo
     const float* xf = dec ? w.x2 : w.x1;
     const Norm& nf = dec ? P.ln3 : P.ln2;
     // feed-forward block:  dz = dY W2^T * [a > 0];  dv = dz W1^T;  dW2, dW1 (and biases) as jobs
-    // flush(0): after each weight-gradient job; flush(1): after the feed-forward block
+    // flush(0): after each weight-gradient job (true: the layer's last); flush(1): after the feed-forward block
     jobs.push_back({&P.ffn2, w.a, ine, T});
     GP_TRY(flush(0));
     GP_TRY(linear_dx(c, P.ffn2, ine, T, dz, EPI_RELU_MASK, w.a, 0));
@@ -1319,7 +1325,7 @@ gp_status layer_backward(const Ctx& c, int set, int half, int l, bool first, flo
     a.delta = b.delta;
     GP_TRY(timed_attention(c, GP_K_ATTN_BWD, a, true));
     jobs.push_back({&P.qkv, w.u, dqkv, T});
-    GP_TRY(flush(0));
+    GP_TRY(flush(0, true));
     GP_TRY(linear_dx(c, P.qkv, dqkv, T, b.dn, EPI_F32, nullptr, 0, true));
     const float* x_in = p->xs[set][l];
     if (dxe_final || dx32_final || l == 0) {
@@ -2145,10 +2151,10 @@ gp_status gp_backward_microbatch_remat(gp_partition* p, int mb, const void* dy_o
         void* oute = nullptr;
         jobs.clear();
         // launch the collected weight-gradient GEMMs (after everything enqueued on main so far)
-        auto flush = [&](int level) -> gp_status {
+        auto flush = [&](int level, bool last = false) -> gp_status {
             if (!run_dw) jobs.clear();  // the group's lowest member runs them
             if (jobs.empty() || level < p->dw_flush) return GP_OK;
-            if (p->dw_flush < 0 && level < 2) {
+            if (p->dw_flush < 0 && !last && level < 2) {
                 long tiles = 0;
                 for (const DwJob& j : jobs) tiles += (long)((j.L->in + 127) / 128) * ((j.L->out + 127) / 128);
                 if (tiles < 512) return GP_OK;
