@@ -317,8 +317,10 @@ gp_status gp_stream_destroy(gp_stream stream);
 gp_status gp_accumulate_and_step(gp_partition* p, float lr, double* loss_out, gp_stream stream);
 
 /*
- * Launch timers (instrumentation; not part of the method).  Each library
- * launch belongs to one role: a linear layer's forward ("FWD", Y = X W + b),
+ * Launch timers (instrumentation; not part of the method).  Selecting a role
+ * changes no launch.  Each library launch belongs to one role (a launch of
+ * several weight gradients at once to one role each: it is bracketed once, its
+ * time divided over them in proportion to their FLOPs): a linear layer's forward ("FWD", Y = X W + b),
  * input-gradient ("DX", dX = dY W^T) or weight-gradient ("DW", G_W += X^T dY
  * with the bias gradient fused) GEMM, including its split-K reduction when
  * one is used; an attention forward or backward; a LayerNorm forward or

@@ -198,7 +198,12 @@ struct LaunchTimer {
     bool markers = false;  // GP_TIMER_MARKERS=1: also launch role_marker around each timed launch
     int every = 1;         // time one launch in `every` of a selected role
     long seen[GP_K_COUNT] = {};  // launches of each selected role since the last reset
-    std::vector<std::pair<hipEvent_t, hipEvent_t>> recs[GP_K_COUNT];
+    struct Rec {
+        hipEvent_t first, second;
+        double share;  // of the time between them that is the role's
+        bool owner;    // of the events (several roles may share a launch)
+    };
+    std::vector<Rec> recs[GP_K_COUNT];
     double flops[GP_K_COUNT] = {}, bytes[GP_K_COUNT] = {};
     std::vector<hipEvent_t> pool;  // created events not in use
     std::vector<hipEvent_t> all;   // every created event (destroyed with the partition)
@@ -218,7 +223,8 @@ struct LaunchTimer {
     }
     void reset() {
         for (int r = 0; r < GP_K_COUNT; ++r) {
-            for (auto& pr : recs[r]) {
+            for (const Rec& pr : recs[r]) {
+                if (!pr.owner) continue;
                 pool.push_back(pr.first);
                 pool.push_back(pr.second);
             }
@@ -722,18 +728,32 @@ Ctx make_ctx(gp_partition* p, hipStream_t st, Lane lane = Lane::Main) {
         if (s_ != GP_OK) return s_;  \
     } while (0)
 
-// Run `launch` (which enqueues on c.st); when `role` is being timed (and this
-// is a sampled launch of it), bracket it with two events on c.st and add its
-// algorithmic work.
+// A role's algorithmic work in a launch.
+struct RoleWork {
+    int role;
+    double flops, bytes;
+};
+
+// Run `launch` (which enqueues on c.st), the work of the n roles at `w`; when any
+// of them is being timed (and this is a sampled launch of it), bracket it with two
+// events on c.st and add the role's algorithmic work.  Roles that share a launch
+// share its time in proportion to their FLOPs; the trace's markers label a launch
+// of one role only.
 template <class F>
-gp_status timed(const Ctx& c, int role, double flops, double bytes, F&& launch) {
+gp_status timed(const Ctx& c, const RoleWork* w, int n, F&& launch) {
     LaunchTimer& t = c.p->timer;
-    if (!t.on(role)) return launch();
-    if (t.seen[role]++ % t.every != 0) return launch();
+    const RoleWork* on[8];
+    int m = 0;
+    double flops = 0.0;
+    for (int i = 0; i < n; ++i) {
+        flops += w[i].flops;
+        if (t.on(w[i].role) && t.seen[w[i].role]++ % t.every == 0) on[m++] = &w[i];
+    }
+    if (m == 0) return launch();
     hipEvent_t e0, e1;
     GP_TRY(t.take(e0));
     GP_TRY(t.take(e1));
-    if (t.markers) GP_TRY(role_marker(role, 0, c.st));
+    if (t.markers && n == 1) GP_TRY(role_marker(w->role, 0, c.st));
     // the events ride on the role's own kernel dispatches (klaunch)
     LaunchEvents& ev = launch_events();
     ev.start = e0;
@@ -742,16 +762,23 @@ gp_status timed(const Ctx& c, int role, double flops, double bytes, F&& launch) 
     const gp_status s = launch();
     const bool launched = ev.started;
     ev = LaunchEvents();
-    if (t.markers) GP_TRY(role_marker(role, 1, c.st));
+    if (t.markers && n == 1) GP_TRY(role_marker(w->role, 1, c.st));
     if (launched) {
-        t.recs[role].emplace_back(e0, e1);
-        t.flops[role] += flops;
-        t.bytes[role] += bytes;
+        for (int i = 0; i < m; ++i) {
+            t.recs[on[i]->role].push_back({e0, e1, n == 1 ? 1.0 : on[i]->flops / flops, i == 0});
+            t.flops[on[i]->role] += on[i]->flops;
+            t.bytes[on[i]->role] += on[i]->bytes;
+        }
     } else {
         t.pool.push_back(e0);
         t.pool.push_back(e1);
     }
     return s;
+}
+template <class F>
+gp_status timed(const Ctx& c, int role, double flops, double bytes, F&& launch) {
+    const RoleWork w{role, flops, bytes};
+    return timed(c, &w, 1, launch);
 }
 
 // Algorithmic bytes of a GEMM: operands read once, outputs written once (and
@@ -979,20 +1006,22 @@ gp_status linear_dw(const Ctx& c, const DwJob& j, int accumulate) {
     return timed_gemm(c, j.L->role + 2, dw_args(c, j, accumulate), EPI_ACC_F32, false);
 }
 
-// The collected weight gradients: one launch in bf16, unless a tile is forced
-// or one of their roles is being timed (a launch belongs to one role).
+// The collected weight gradients: one launch in bf16, unless a tile is forced.
 gp_status run_dw_jobs(const Ctx& c, const std::vector<DwJob>& jobs, int accumulate) {
-    bool group = c.dt == GP_BF16 && jobs.size() > 1 && jobs.size() <= 8 && c.p->gemm_tile < 0;
-    for (const DwJob& j : jobs) group = group && !c.p->timer.on(j.L->role + 2);
-    if (!group) {
+    if (c.dt != GP_BF16 || jobs.size() < 2 || jobs.size() > 8 || c.p->gemm_tile >= 0) {
         for (const DwJob& j : jobs) GP_TRY(linear_dw(c, j, accumulate));
         return GP_OK;
     }
     GP_TRY(flush_pending(c));
     GemmArgs g[8];
+    RoleWork w[8];
     int n = 0;
-    for (const DwJob& j : jobs) g[n++] = dw_args(c, j, accumulate);
-    return gemm_dw_group(g, n, c.st);
+    for (const DwJob& j : jobs) {
+        g[n] = dw_args(c, j, accumulate);
+        w[n] = {j.L->role + 2, 2.0 * g[n].M * g[n].N * (double)g[n].K, gemm_bytes(g[n], EPI_ACC_F32, c.p->esz)};
+        ++n;
+    }
+    return timed(c, w, n, [&] { return gemm_dw_group(g, n, c.st); });
 }
 
 // LayerNorm backward: dx, and the gamma/beta gradient partials added into
@@ -1838,7 +1867,7 @@ gp_status gp_timer_read(gp_partition* p, int role, double* ms, long* launches, d
     for (const auto& pr : recs) {
         float t = 0.f;
         GP_HIP(hipEventElapsedTime(&t, pr.first, pr.second));
-        total += t;
+        total += t * pr.share;
     }
     if (ms) *ms = total;
     if (launches) *launches = (long)recs.size();

@@ -76,3 +76,37 @@ def test_ragged_reductions_equal_the_register_staged_kernel(cfg, monkeypatch):
             assert np.linalg.norm(v - res[k]) <= 1.2e-4 * np.linalg.norm(v), k
         elif k.split(".")[-1] not in ("bk", "xbk"):  # zero but for rounding
             assert np.array_equal(v, res[k]), k
+
+
+def test_timed_groups_are_the_launches_of_an_untimed_step():
+    """A selected role times the grouped launch itself: the roles share its time
+    by their FLOPs (o : qkv : ffn = 1 : 3 : 4), each counts one launch per layer and
+    pair, and the gradients keep their bits."""
+    from paper_1811_06965_amd.runtime import Partition
+    cfg = _cfg("timed", d_model=256, heads=4, d_ff=1024, seq=256, batch=8, micro=4)
+    case = synth.make_case(cfg, 5, perturb=True)
+    ref = _step(cfg, case)
+    with Partition(cfg) as part:
+        part.load_params(case["layers"], case["head"])
+        inp = part.device_inputs(case)
+        part.timer_select("all")
+        part.step(inp["x"], inp["mem"], inp["dy"])
+        torch.cuda.synchronize()
+        got = {r: part.timer_read(r + ".dw") for r in ("o", "qkv", "ffn1", "ffn2")}
+        part.timer_reset()
+        part.timer_select("o.dw")
+        part.timer_sample(2)
+        out = part.step(inp["x"], inp["mem"], inp["dy"])
+        torch.cuda.synchronize()
+        part.timer_select(None)
+        sampled = part.timer_read("o.dw")
+        gl, _ = part.grads()
+    for role, n in (("o", 1), ("qkv", 3), ("ffn1", 4), ("ffn2", 4)):
+        assert got[role]["launches"] == 4
+        assert got[role]["flops"] == pytest.approx(n * 4 * 2 * 1024 * 256 * 256)
+        assert got[role]["ms"] == pytest.approx(n * got["o"]["ms"]) and got[role]["ms"] > 0
+    assert sampled["launches"] == 2 and 0 < sampled["ms"]
+    assert np.array_equal(to_np(out["dx"]), ref["dx"])
+    for l, g in enumerate(gl):
+        for k, v in g.items():
+            assert np.array_equal(v, ref[f"{l}.{k}"]), (l, k)
