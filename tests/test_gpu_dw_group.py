@@ -25,8 +25,15 @@ CASES = [
     _cfg("decoder", kind="decoder", mem_seq=64, batch=4, micro=2, d_model=128, heads=2, d_ff=392),
     _cfg("decoder_m1", kind="decoder", seq=64, mem_seq=32, batch=3, micro=1, loss="xent_ls", vocab=136,
          label_smoothing=0.1),
-    # a group large enough to be handed over before the layer's end
+    # reductions over 2 x 1024 and 768 rows that single launches split
+    _cfg("rows2048", layers=1, d_model=256, heads=4, d_ff=512, seq=256, batch=8, micro=2),
+    _cfg("rows768_m3", layers=1, d_model=128, heads=2, d_ff=512, seq=256, batch=9, micro=3),
+    # jobs large enough to be handed over alone, and a group of the rest
     _cfg("wide", layers=1, d_model=1024, heads=16, d_ff=8192 + 8, seq=32, batch=2, micro=2),
+    # jobs that are large enough only together: a group handed over in the middle of the layer, and one of the rest
+    _cfg("two_groups", layers=1, d_model=1024, heads=16, d_ff=4096 + 8, seq=32, batch=2, micro=2),
+    _cfg("two_groups_decoder", layers=1, d_model=1024, heads=16, d_ff=4096 - 40, seq=32, mem_seq=64, batch=2, micro=2,
+         kind="decoder"),
 ]
 
 
@@ -48,11 +55,11 @@ def _step(cfg, case):
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
 def test_grouped_weight_gradients_equal_single_launches(cfg, monkeypatch):
-    """Fewer than eight k-tiles per reduction over rows: no launch splits it, so
-    the grouping changes no bit."""
+    """A group adds up each reduction as its own launch does, split over workgroups
+    or not, so neither the grouping nor the time of the hand-over changes a bit."""
     case = synth.make_case(cfg, 5, perturb=True)
     ref = _step(cfg, case)
-    for flush in ("0", "2"):
+    for flush in ("0", "1", "2"):
         monkeypatch.setenv("GP_DW_FLUSH", flush)
         res = _step(cfg, case)
         for k, v in ref.items():
