@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 #include "../../include/gp.h"
+#include "sched.hpp"  // UpdateLinear
 
 namespace gp {
 
@@ -167,13 +168,6 @@ gp_status refresh_linear(int dtype, const float* w, int in, int out, void* kn, v
                          hipStream_t st, bool nk16 = false);
 // The rows of nk [out, in] (bf16) in fp4, as refresh_linear's q4 / q4s.
 gp_status quantize_rows_fp4(const void* nk, int out, int in, void* q4, void* q4s, hipStream_t st);
-// A linear of the update's table (device memory): its float offset in master /
-// grads / ms, the element offsets of its working copies, and the number of 64 x
-// 64 tiles of the linears before it.
-struct UpdateLinear {
-    long w, kn, nk;
-    int in, out, tile0, nk16;
-};
 // The SGD (ms == nullptr) or RMSProp step of linears l0 .. l1 - 1 (`tiles` tiles)
 // fused with the refresh of their working copies as refresh_linear makes them
 // (fp4 copies excepted), and of nranges float ranges (offset, count pairs in

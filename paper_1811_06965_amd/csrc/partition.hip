@@ -1493,44 +1493,20 @@ void free_all(gp_partition* p) {
 }
 
 // The update's tables (see gp_partition::upd_tab) from the parameter plan.
-hipError_t build_update_tables(gp_partition* p) {
-    std::vector<UpdateLinear> tab;
-    std::vector<long> ranges;
-    auto range = [&](size_t off, long n) {
-        for (long i = 0; i < n; i += 1024) {
-            ranges.push_back((long)off + i);
-            ranges.push_back(std::min(1024L, n - i));
-        }
-    };
-    int tiles = 0;
-    p->upd_apart = p->g.dtype == GP_BF16;
-    p->upd_tile0.clear();
-    p->upd_layer.clear();
-    auto linear = [&](const Linear& l) {
-        if (!l.present) return;
-        tab.push_back({(long)l.w, (long)l.kn, (long)l.nk, l.in, l.out, tiles, l.f16 ? 1 : 0});
-        p->upd_tile0.push_back(tiles);
-        if (l.in % 64 || l.out % 64) p->upd_apart = 0;
-        tiles += ((l.in + 63) / 64) * ((l.out + 63) / 64);
-        range(l.b, l.out);
-    };
-    for (const LayerPlan& P : p->plan.layers) {
-        p->upd_layer.push_back((int)tab.size());
-        for (const Linear* l : {&P.qkv, &P.o, &P.ffn1, &P.ffn2, &P.xq, &P.xkv, &P.xo}) linear(*l);
-    }
-    p->upd_layer.push_back((int)tab.size());
-    linear(p->plan.head.out);
-    p->upd_tile0.push_back(tiles);
-    for (const Norm* n : p->plan.norms()) {
-        range(n->g, n->n);
-        range(n->b, n->n);
-    }
-    hipError_t e = hipMalloc((void**)&p->upd_tab, tab.size() * sizeof(UpdateLinear));
-    if (e == hipSuccess) e = hipMemcpy(p->upd_tab, tab.data(), tab.size() * sizeof(UpdateLinear), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->upd_ranges, ranges.size() * sizeof(long));
-    if (e == hipSuccess) e = hipMemcpy(p->upd_ranges, ranges.data(), ranges.size() * sizeof(long), hipMemcpyHostToDevice);
-    p->n_upd_ranges = (int)(ranges.size() / 2);
-    return e;
+gp_status build_update_tables(gp_partition* p) {
+    UpdateTables t;
+    if (!plan_update_tables(p->plan, t))
+        return set_error(GP_ERR_STATE, "internal: the update's tables miss a parameter or hold one twice");
+    p->upd_tile0 = t.tile0;
+    p->upd_layer = t.layer;
+    p->upd_apart = p->g.dtype == GP_BF16 && t.whole;
+    p->n_upd_ranges = (int)(t.ranges.size() / 2);
+    const size_t lb = t.linears.size() * sizeof(UpdateLinear), rb = t.ranges.size() * sizeof(long);
+    GP_HIP(hipMalloc((void**)&p->upd_tab, lb));
+    GP_HIP(hipMemcpy(p->upd_tab, t.linears.data(), lb, hipMemcpyHostToDevice));
+    GP_HIP(hipMalloc((void**)&p->upd_ranges, rb));
+    GP_HIP(hipMemcpy(p->upd_ranges, t.ranges.data(), rb, hipMemcpyHostToDevice));
+    return GP_OK;
 }
 
 gp_status alloc(void** ptr, size_t bytes) {
@@ -1750,10 +1726,14 @@ gp_status gp_partition_configure(gp_partition* p, const gp_config* cfg) {
     if (e == hipSuccess) e = hipMemset(p->grads, 0, p->plan.n32 * 4);
     if (e == hipSuccess) e = hipMemset(p->ws, 0, p->bytes_ws);
     if (e == hipSuccess && p->opt_ms) e = hipMemset(p->opt_ms, 0, p->plan.n32 * 4);
-    if (e == hipSuccess) e = build_update_tables(p);
     if (e != hipSuccess) {
         free_all(p);
         return hip_fail(e, __FILE__, __LINE__);
+    }
+    s = build_update_tables(p);
+    if (s != GP_OK) {
+        free_all(p);
+        return s;
     }
     for (const Linear* l : p->plan.linears()) {
         s = refresh_linear(g.dtype, p->master + l->w, l->in, l->out, p->W(l->kn), p->W(l->nk),

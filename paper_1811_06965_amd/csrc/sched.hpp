@@ -278,46 +278,65 @@ inline ParamPlan plan_params(const Dims& d, const Geometry& g) {
     return p;
 }
 
-// The parameters outside the linears' weights (biases, LayerNorm gains and
-// shifts) as (offset, count) float ranges, written to `ranges` as flat pairs,
-// with a check of the plan: returns false (and leaves `ranges` empty) unless
-// every linear is a whole number of 64 x 64 tiles and the weights and ranges
-// together cover the n32 master floats exactly once.  The update itself takes
-// any plan (its tables are built with the partition); the host tests use this
-// to show that a plan leaves no gap and no overlap.
-inline bool plan_update_ranges(const ParamPlan& p, std::vector<long>& ranges) {
-    ranges.clear();
-    std::vector<std::pair<size_t, size_t>> cover;  // (offset, count) of every block
-    for (const Linear* l : p.linears()) {
-        if (l->in % 64 || l->out % 64) {
-            ranges.clear();
-            return false;
+// A linear of the update's table (see update_linears): its float offset in master /
+// grads / ms, the element offsets of its working copies, and the number of 64 x 64
+// tiles of the linears before it.
+struct UpdateLinear {
+    long w, kn, nk;
+    int in, out, tile0, nk16;
+};
+// What the update goes over: the linears in plan order, and the other parameters
+// (biases, LayerNorm gains and shifts) as (offset, count) float ranges of at most
+// 1024, as flat pairs.
+struct UpdateTables {
+    std::vector<UpdateLinear> linears;
+    std::vector<long> ranges;
+    std::vector<int> tile0;  // per linear, then the total
+    std::vector<int> layer;  // first linear of each layer, then of the head
+    bool whole = true;       // every linear is a whole number of tiles
+};
+
+// Returns false unless the linears' weights and the ranges take every parameter of
+// the plan exactly once.
+inline bool plan_update_tables(const ParamPlan& p, UpdateTables& t) {
+    t = UpdateTables{};
+    auto range = [&](size_t off, long n) {
+        for (long i = 0; i < n; i += 1024) {
+            t.ranges.push_back((long)off + i);
+            t.ranges.push_back(std::min(1024L, n - i));
         }
-        cover.push_back({l->w, (size_t)l->in * l->out});
-        cover.push_back({l->b, (size_t)l->out});
-        ranges.push_back((long)l->b);
-        ranges.push_back(l->out);
+    };
+    int tiles = 0;
+    auto linear = [&](const Linear& l) {
+        if (!l.present) return;
+        t.linears.push_back({(long)l.w, (long)l.kn, (long)l.nk, l.in, l.out, tiles, l.f16 ? 1 : 0});
+        t.tile0.push_back(tiles);
+        t.whole = t.whole && l.in % 64 == 0 && l.out % 64 == 0;
+        tiles += ((l.in + 63) / 64) * ((l.out + 63) / 64);
+        range(l.b, l.out);
+    };
+    for (const LayerPlan& P : p.layers) {
+        t.layer.push_back((int)t.linears.size());
+        for (const Linear* l : {&P.qkv, &P.o, &P.ffn1, &P.ffn2, &P.xq, &P.xkv, &P.xo}) linear(*l);
     }
+    t.layer.push_back((int)t.linears.size());
+    linear(p.head.out);
+    t.tile0.push_back(tiles);
     for (const Norm* n : p.norms()) {
-        if (n->b != n->g + (size_t)n->n) {  // gains then shifts, contiguous
-            ranges.clear();
-            return false;
-        }
-        cover.push_back({n->g, 2 * (size_t)n->n});
-        ranges.push_back((long)n->g);
-        ranges.push_back(2L * n->n);
+        range(n->g, n->n);
+        range(n->b, n->n);
     }
+    std::vector<std::pair<size_t, size_t>> cover;  // (offset, count)
+    for (const UpdateLinear& u : t.linears) cover.push_back({(size_t)u.w, (size_t)u.in * u.out});
+    for (size_t i = 0; i < t.ranges.size(); i += 2) cover.push_back({(size_t)t.ranges[i], (size_t)t.ranges[i + 1]});
     std::sort(cover.begin(), cover.end());
-    size_t end = 0;
+    size_t end = 0, sum = 0;
     for (const auto& c : cover) {
-        if (c.first != end) {  // a gap (padding) or an overlap
-            ranges.clear();
-            return false;
-        }
+        if (c.first < end) return false;  // an overlap
         end = c.first + c.second;
+        sum += c.second;
     }
-    if (end != p.n32) ranges.clear();
-    return end == p.n32;
+    return end <= p.n32 && sum == p.count;  // padding between the blocks is nobody's
 }
 
 // Where one logical parameter tensor lives in the fp32 master: `rows` rows of

@@ -82,16 +82,33 @@ int main() {
     const size_t cross = 4 * 1024 * 1024 + 4 * 1024 + 2 * 1024;
     CHECK(pd.count == 16 * (per_layer + cross) + 2 * 1024 + 1024 * 32000 + 32000, "plan_count_decoder_head");
 
-    // ---- the bf16 update's range table: weights in tiles, every other parameter in a range
-    std::vector<long> ranges;
-    CHECK(plan_update_ranges(p, ranges) && ranges.size() == 2 * (4 * 16 + 2 * 16), "update_ranges_encoder");
-    bool biases = true;
-    for (size_t i = 0; i < ranges.size(); i += 2) biases = biases && ranges[i] % 64 == 0 && ranges[i + 1] > 0;
-    CHECK(biases && ranges[0] == (long)p.layers[0].qkv.b && ranges[1] == 3 * 1024, "update_ranges_first_bias");
-    CHECK(plan_update_ranges(pd, ranges) && ranges.size() == 2 * (7 * 16 + 3 * 16 + 2), "update_ranges_decoder_head");
+    // ---- the update's tables: weights in tiles, every other parameter in a range, each once
+    UpdateTables u;
+    CHECK(plan_update_tables(p, u) && u.whole && u.linears.size() == 4 * 16, "update_tables_encoder");
+    CHECK(u.ranges[0] == (long)p.layers[0].qkv.b && u.ranges[1] == 1024 && u.ranges[3] == 1024 && u.ranges[5] == 1024,
+          "update_tables_first_bias");
+    bool tiles = true, cut = true;
+    for (size_t i = 0; i < u.linears.size(); ++i)
+        tiles = tiles && u.linears[i].tile0 == u.tile0[i] &&
+                u.tile0[i + 1] - u.tile0[i] == ((u.linears[i].in + 63) / 64) * ((u.linears[i].out + 63) / 64);
+    for (size_t i = 1; i < u.ranges.size(); i += 2) cut = cut && u.ranges[i] > 0 && u.ranges[i] <= 1024;
+    CHECK(tiles && cut, "update_tables_tiles_and_cuts");
+    CHECK(u.layer.size() == 17 && u.layer[3] == 12 && u.layer[16] == 64, "update_tables_layers");
+    CHECK(plan_update_tables(pd, u) && u.whole && u.linears.size() == 7 * 16 + 1 && u.layer[16] == 7 * 16,
+          "update_tables_decoder_head");
     Geometry gv = gd; gv.V = 1000;  // a head that is not a whole number of 64-wide tiles
-    CHECK(!plan_update_ranges(plan_params(d, gv), ranges) && ranges.empty(), "update_ranges_ragged_head");
-    CHECK(!plan_update_ranges(plan_params(d3, g), ranges) && ranges.empty(), "update_ranges_ragged_widths");
+    CHECK(plan_update_tables(plan_params(d, gv), u) && !u.whole, "update_tables_ragged_head");
+    CHECK(plan_update_tables(plan_params(d3, g), u) && !u.whole, "update_tables_ragged_widths");
+    CHECK(plan_update_tables(plan_params(d3, gv), u) && !u.whole, "update_tables_ragged_decoder_head");
+    ParamPlan twice = p;  // a plan whose blocks overlap
+    twice.layers[2].o.w = twice.layers[2].qkv.w + 64;
+    CHECK(!plan_update_tables(twice, u), "update_tables_overlap");
+    ParamPlan missing = pd;  // a linear the table leaves out
+    missing.layers[5].xq.present = false;
+    CHECK(!plan_update_tables(missing, u), "update_tables_missing_linear");
+    missing = p;
+    missing.layers[15].ln2.n -= 1;
+    CHECK(!plan_update_tables(missing, u), "update_tables_missing_gain");
 
     // ---- parameter resolution: q/k/v are column slices of the packed projection
     ParamRef r;
