@@ -7,11 +7,14 @@
 //   input grad dX = dY W^T   A = dY [T, out] k-contiguous,  B = W   [in, out]  k-contiguous
 //   weight grad dW = X^T dY  A = X  [T, in]  m-contiguous,  B = dY  [T, out]   n-contiguous
 // The partition keeps both W and W^T working copies so the two activation
-// GEMMs stream both operands along k.  The weight-gradient GEMM loads
-// m-contiguous 16-byte vectors over 4 consecutive k and transposes them in
-// registers, so LDS always holds k-contiguous rows and every MFMA fragment is
-// one 16-byte LDS read per lane.
+// GEMMs stream both operands along k.  Every problem runs on the direct-to-LDS
+// kernels below (gemm_dl, gemm_dw_group).
 //
+// gemm_kernel, the register-staged form, runs only where GP_GEMM_TILE = 0..3 asks
+// for it: the simpler kernel that the others' tests compare with.  Its
+// weight-gradient form loads m-contiguous 16-byte vectors over 4 consecutive k and
+// transposes them in registers, so LDS always holds k-contiguous rows and every
+// MFMA fragment is one 16-byte LDS read per lane.
 // Workgroup = 4 waves (2 x 2).  Tile shapes (bf16, BK = 64):
 //   256 x 256: each wave 128 x 128 = 4 x 4 blocks of v_mfma_f32_32x32x16_bf16
 //              (256 accumulator registers per lane, held in AGPRs); 144 KB LDS
@@ -167,13 +170,8 @@ struct TileLoader {
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) {
                     char* dst = s + lds_byte(mb * VEC + i, kb * KB * ESZ);
-                    if constexpr (sizeof(T) == 2) {
-                        bf16x4 v = {r[p * KB + 0][i], r[p * KB + 1][i], r[p * KB + 2][i], r[p * KB + 3][i]};
-                        *reinterpret_cast<bf16x4*>(dst) = v;
-                    } else {
-                        f32x4 v = {r[p * KB + 0][i], r[p * KB + 1][i], r[p * KB + 2][i], r[p * KB + 3][i]};
-                        *reinterpret_cast<f32x4*>(dst) = v;
-                    }
+                    bf16x4 v = {r[p * KB + 0][i], r[p * KB + 1][i], r[p * KB + 2][i], r[p * KB + 3][i]};
+                    *reinterpret_cast<bf16x4*>(dst) = v;
                 }
             }
         }
@@ -1238,7 +1236,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_v4(GemmArgs args, int split
 }
 
 enum TileCfg {
-    T256x256 = 0, T256x128 = 1, T128x256 = 2, T128x128 = 3,  // register-staged (any operand form)
+    T256x256 = 0, T256x128 = 1, T128x256 = 2, T128x128 = 3,  // register-staged, forced only
     T_DL128x128_S2 = 4, T_DL128x128_S3 = 5, T_DL256x128_S2 = 6, T_DL256x256_S2 = 7,  // direct-to-LDS, k-contiguous
     T_DL256x256_W8 = 8, T_DL256x128_W8 = 9, T_DL128x256_W8 = 10,                          // ... with 8 waves
     T_DL128x128_W8A = 11, T_DL128x128_W8B = 12, T_DL256x128_W8S3 = 13, T_DL128x256_W8S3 = 14,

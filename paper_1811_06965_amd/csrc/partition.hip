@@ -343,8 +343,9 @@ struct gp_partition {
     BwdWs bw;
     BwdWs bw1;  // the odd backward lane's scratch (p32, q32, dn, dc, delta, dmem32, splitk, v16)
     size_t bytes_params = 0, bytes_grads = 0, bytes_stash = 0, bytes_ws = 0;
-    // GEMM tile-shape override (GP_GEMM_TILE = 0..10, GP_GEMM_SPLITS), read at
-    // configure; -1 lets the library choose per problem.
+    // GEMM tile-shape override (GP_GEMM_TILE = 0..23: the bf16 shapes of gemm.hip's
+    // TileCfg, 32..34: the fp32 tiles; GP_GEMM_SPLITS), read at configure; -1 lets
+    // the library choose per problem.
     int gemm_tile = -1, gemm_splits = 0;
     LaunchTimer timer;
     // Weight-gradient GEMMs run on a second stream (GP_SIDE_STREAM=0 turns it
